@@ -234,7 +234,7 @@ def main():
         if pmc.get("src_hash") == src_hash():
             traffic = pmc.get("hbm_bytes_per_launch")
     # the product kernel each op ran, from the plan's tuning (group_rows)
-    kname = {0: "k_spmm", 1: "k_spmm_grp", 2: "k_spmm_flat", 3: "k_spmm_win"}
+    kname = {0: "k_spmm", 1: "k_walk", 2: "k_walk", 3: "k_spmm_win"}
     kf = kname[shiro.get_tuning(plan, "spmm", N, tdt)["group_rows"]]
     tb = shiro.get_tuning(plan, "spmm_t", N, tdt)
     kb = kname[tb["group_rows"]]

@@ -134,16 +134,19 @@ typedef struct {
  * row-based scheme's partial rows and sum). */
 typedef struct {
   int32_t chunk;     /* merge-path items (rows + nonzeros) per wavefront       */
-  int32_t lanes;     /* lanes sharing one dense row: 8, 16, 32 or 64 (tile width = lanes * 16 bytes) */
-  int32_t unroll;    /* nonzeros in flight per lane group: 1, 2 or 4           */
-  int32_t group_rows; /* 0: a wavefront per row; 1: each lane group of a
-                       * wavefront owns its own rows; 2: each lane group walks
-                       * its own chunks nonzero by nonzero across row ends;
-                       * 3: the same walk with its index, row and value streams
-                       * loaded a window of `lanes` nonzeros at a time (2 and 3
-                       * not for the sampled product, SHIRO_KERNEL_SDDMM)      */
+  int32_t lanes;     /* lanes sharing one dense row: 8, 16, 32 or 64 (tile width =
+                      * lanes * 16 bytes; the nonzero walk has tiles of 256 bytes,
+                      * up to 16, or 512)                                       */
+  int32_t unroll;    /* nonzeros in flight per lane group: 1, 2 or 4 (not the
+                      * nonzero walk)                                           */
+  int32_t group_rows; /* 0: a wavefront per row, its lane groups on the row's
+                      * nonzeros; 1 or 2: the nonzero walk, a wavefront per
+                      * chunk, every lane on every gathered row; 3: the windowed
+                      * walk, each lane group of a wavefront on its own chunks.
+                      * Sampled product (SHIRO_KERNEL_SDDMM): 0 or 1            */
   int32_t xcd_remap; /* 1: give each XCD a contiguous range of work            */
-  int32_t wg_per_cu; /* persistent grid: workgroups per compute unit           */
+  int32_t wg_per_cu; /* persistent grid: workgroups per compute unit (not the
+                      * nonzero walk, whose grid holds every chunk)             */
   int32_t lds_rows;  /* windowed walk (group_rows 3) of SHIRO_KERNEL_SPMM and
                       * SHIRO_KERNEL_SPMM_T only: the lds_rows most referenced
                       * rows of the gathered operand (Bpacked, resp. dY) are

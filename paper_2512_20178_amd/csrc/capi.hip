@@ -207,11 +207,20 @@ int ensure_acc32(shiro_plan plan, int64_t elems, bool allocate) {
 }
 
 int ensure_tvals(shiro_plan plan, bool allocate) {
-  if (plan->tvals_elems >= plan->nnz && plan->tvals) return SHIRO_OK;
+  if (plan->tvals) return SHIRO_OK;
   if (!allocate) return set_error(SHIRO_ERR_CAPTURING, "transposed values buffer not prepared before capture");
-  SHIRO_TRY(dev_alloc_n(&plan->tvals, std::max<int64_t>(plan->nnz, 1)));
-  SHIRO_TRY(dev_alloc_n(&plan->tdvals, std::max<int64_t>(plan->nnz, 1)));
-  plan->tvals_elems = plan->nnz;
+  return dev_alloc_n(&plan->tvals, std::max<int64_t>(plan->nnz, 1));
+}
+
+int ensure_tdvals(shiro_plan plan, int tiles, bool allocate) {
+  if (plan->tdvals_tiles >= tiles) return SHIRO_OK;
+  if (!allocate) return set_error(SHIRO_ERR_CAPTURING, "value gradients buffer not prepared before capture");
+  SHIRO_HIP(hipDeviceSynchronize());
+  retire_buffer(plan, plan->tdvals);
+  plan->tdvals = nullptr;
+  plan->tdvals_tiles = 0;
+  SHIRO_TRY(dev_alloc_n(&plan->tdvals, std::max<int64_t>(plan->nnz, 1) * tiles));
+  plan->tdvals_tiles = tiles;
   return SHIRO_OK;
 }
 
@@ -435,7 +444,7 @@ static int time_candidate(hipStream_t s, F&& run, float* ms_out) {
 
 // Chunk size at which a persistent grid of wg_per_cu workgroups per CU gives
 // each of its workers m chunks: merge items / (CUs * wg_per_cu * workers per
-// workgroup * m).  Workers are wavefronts, or lane groups for the nonzero
+// workgroup * m).  Workers are wavefronts, or lane groups for the windowed
 // walk; the lanes a lane group uses follow from N as in the launch (the
 // fused backward always asks for one tile).  0 when the items are unknown.
 static int fit_chunk(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt, const shiro_tuning_t& t, int m) {
@@ -450,7 +459,7 @@ static int fit_chunk(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt, con
   int lanes = kernel == SHIRO_KERNEL_SPMM_T ? 64 : t.lanes;
   const int64_t need = ceil_div((int64_t)N, (int64_t)vec);
   while (lanes > 8 && lanes / 2 >= need) lanes /= 2;
-  const int64_t wpb = kWavesPerBlock * (t.group_rows >= 2 ? kWave / lanes : 1);
+  const int64_t wpb = kWavesPerBlock * (t.group_rows == 3 ? kWave / lanes : 1);
   const int64_t workers = (int64_t)plan->num_cus * t.wg_per_cu * wpb * m;
   const int64_t c = ceil_div(items, workers);
   return (int)std::min<int64_t>(std::max<int64_t>(c, 16), 1 << 22);
@@ -508,6 +517,7 @@ static int tune_one(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt, Tune
     for (int lanes : {64, 32, 16})
       for (int wg : {2, 4, 8, 16})
         for (int xcd : {0, 1}) {
+          if (walk && (grp == 1 || (grp == 2 && (wg != 16 || lanes == 64)))) continue;  // the same launch as another candidate
           shiro_tuning_t t = base;
           t.group_rows = grp;
           t.lanes = lanes;
@@ -962,6 +972,7 @@ SHIRO_API int shiro_prepare(shiro_plan plan, int32_t N, shiro_dtype dt, uint32_t
     SHIRO_TRY(build_transposed(plan, s));
     SHIRO_TRY(ensure_tvals(plan, true));
     const shiro_tuning_t t = tuning_for(plan, SHIRO_KERNEL_SPMM_T, N, dt);
+    SHIRO_TRY(ensure_tdvals(plan, is_walk(t) ? walk_dot_tiles(N, dt, t) : 1, true));
     SHIRO_TRY(ensure_cols_work(plan, t.chunk, true, s, &wl));
     SHIRO_TRY(ensure_carry(plan, (int64_t)wl->W * 2 * N, true));
     const HotRows* hot;

@@ -152,8 +152,8 @@ struct shiro_plan_s {
 
   // values and value gradients in transposed order (per backward call)
   float* tvals = nullptr;
-  float* tdvals = nullptr;
-  int64_t tvals_elems = 0;
+  float* tdvals = nullptr;   // one set per column tile of the walk
+  int32_t tdvals_tiles = 0;
 
   // float32 accumulator of the per-block mode when Y is bfloat16
   float* acc32 = nullptr;
@@ -284,10 +284,29 @@ int ensure_cols_work(shiro_plan plan, int32_t chunk, bool allocate, hipStream_t 
 int ensure_carry(shiro_plan plan, int64_t elems, bool allocate);
 int ensure_acc32(shiro_plan plan, int64_t elems, bool allocate);
 int ensure_tvals(shiro_plan plan, bool allocate);
+int ensure_tdvals(shiro_plan plan, int tiles, bool allocate);
 // The hot-row arrays of kernel SHIRO_KERNEL_SPMM or _SPMM_T for H slots
 // (setup: copies the index array to the host; NOT_READY/CAPTURING when
 // allocate is false and they are missing).
 int ensure_hot(shiro_plan plan, int kernel, int32_t H, bool allocate, hipStream_t s, const HotRows** out);
+
+// The nonzero walk (walk.hpp) runs for group_rows 1 and 2.
+inline bool is_walk(const shiro_tuning_t& t) { return t.group_rows == 1 || t.group_rows == 2; }
+// Columns per lane of the walk: the narrowest of 4 and 8 bytes with which 64
+// lanes cover N, 4 where `lanes` asks for tiles of 256 bytes; 2 bytes for a
+// single bfloat16 column (never more columns than N).  16 bytes per lane (one
+// tile of 256 float32 columns) were slower than two tiles: 308 against 257 us
+// on L2-resident rows, 948 against 853 on the 2^24 panel's backward at N = 256.
+inline int walk_vec(int32_t N, shiro_dtype dt, int lanes) {
+  const int unit = dt == SHIRO_F32 ? 1 : 2;  // elements in 4 bytes
+  if (N < unit) return 1;
+  return N > kWave * unit && lanes >= 32 ? 2 * unit : unit;
+}
+// Column tiles of the walk with dots; 0: more than four, not fused.
+inline int walk_dot_tiles(int32_t N, shiro_dtype dt, const shiro_tuning_t& t) {
+  const int64_t n = ceil_div(N, (int64_t)kWave * walk_vec(N, dt, t.lanes));
+  return n <= 4 ? (int)n : 0;
+}
 
 shiro_tuning_t default_tuning(int kernel, int32_t N, shiro_dtype dt);
 // The tuning a plan uses for one kernel family (its own, else the default).

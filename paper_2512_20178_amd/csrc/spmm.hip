@@ -10,17 +10,19 @@
 // output epilogue once.  No floating-point atomics anywhere, so every output
 // is reproducible bit for bit.
 //
-// Lane layout: a dense row is read 16 bytes per lane by `LANES` lanes (tile
-// width LANES*16 bytes: 128 float32 columns for 32 lanes); the 64/LANES lane
-// groups of a wavefront take consecutive nonzeros of the same row, UNROLL
-// deep, and are reduced with cross-lane shuffles when the row ends.  All row
-// bookkeeping is wavefront-uniform and lives in scalar registers.
+// Three kernels share these chunks.  The nonzero walk (walk.hpp, the default)
+// gives a wavefront a chunk and every gather to all of its lanes.  In the two
+// of this file a dense row is read 16 bytes per lane by `LANES` lanes (tile
+// width LANES*16 bytes: 128 float32 columns for 32 lanes): in the
+// row kernel the 64/LANES lane groups of a wavefront take consecutive
+// nonzeros of one row, in the windowed walk each has chunks of its own.
 #include <algorithm>
 #include <type_traits>
 #include <vector>
 
 #include "plan.hpp"
 #include "scan.hpp"
+#include "spmm_args.hpp"
 
 namespace shiro {
 
@@ -88,71 +90,24 @@ __global__ void k_gather_vals(const int32_t* __restrict__ perm, const float* __r
     out[j] = vals[perm[j]];
 }
 
+// in: one set of partial dots per column tile, n apart.
+//
 // One value per thread: with four per thread (16-byte index loads) the
 // scattered stores ran slower on the MI355X (55 against 44 us for 4.2M
 // values), as did a gather through the inverse permutation.
-__global__ void k_scatter_vals(const int32_t* __restrict__ perm, const float* __restrict__ in,
-                               int64_t nnz, float* __restrict__ out) {
-  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz;
-       j += (int64_t)gridDim.x * blockDim.x)
-    out[perm[j]] = in[j];
+__global__ void k_scatter_vals(const int32_t* __restrict__ perm, const float* __restrict__ in, int tiles,
+                               int64_t n, float* __restrict__ out) {
+  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n;
+       j += (int64_t)gridDim.x * blockDim.x) {
+    float s = in[j];
+    for (int t = 1; t < tiles; ++t) s += in[j + t * n];
+    out[perm[j]] = s;
+  }
 }
 
 // ---------------------------------------------------------------------------
 // SpMM: out[r, :] = sum_{k in row r} vals[k] * X[idx[k], :]
 // ---------------------------------------------------------------------------
-// Host-side bundle of the kernel arguments.  The kernels take them as
-// separate __restrict__ parameters: that tells the compiler the pattern
-// arrays are never written, so wave-uniform reads of them (row pointers,
-// chunk bounds) become scalar loads.
-struct SpmmArgs {
-  const int64_t* ptr;       // R + 1
-  const int32_t* idx;       // nnz: row of X to gather
-  const float* vals;        // values in pattern order
-  const void* D;            // optional: dense row per pattern row, dotted with each gathered row
-  int64_t ldd;
-  float* dot_out;           // nnz: the dots, in pattern order (when D is set)
-  const void* X;            // gathered dense rows
-  int64_t ldx;
-  void* out;                // R x N, may be null (transposed: dBpacked optional)
-  int64_t ldo;
-  void* scat;               // transposed only: dB, rows scat_idx[r] (see scat_mode)
-  int64_t lds;
-  int32_t scat_mode;        // 1: add the row into dB, 2: overwrite the dB row
-  const int32_t* scat_idx;  // R
-  const int32_t* chunk_row;  // W + 1
-  const int32_t* chunk_nz;   // W + 1
-  const int32_t* rid;       // nnz: row of each nonzero (only for patterns without empty rows)
-  const int32_t* hot_src;   // windowed walk: rows of X kept in LDS (idx = -(slot + 1) reads slot)
-  int32_t n_hot;
-  float* carry;             // [W][2][N]
-  int32_t W, R, N;
-  int32_t chunks_per_wave;
-  int32_t xcd_remap;
-};
-
-#define SHIRO_SPMM_PARAMS(TIN, TOUT)                                                          \
-  const int64_t *__restrict__ ptr, const int32_t *__restrict__ idx,                           \
-      const float *__restrict__ vals, const TIN *__restrict__ D, int64_t ldd,                 \
-      float *__restrict__ dot_out,                                                            \
-      const TIN *__restrict__ X, int64_t ldx, TOUT *__restrict__ out, int64_t ldo,           \
-      TOUT *__restrict__ scat, int64_t lds, const int32_t *__restrict__ scat_idx,             \
-      const int32_t *__restrict__ chunk_row, const int32_t *__restrict__ chunk_nz,            \
-      const int32_t *__restrict__ rid, float *__restrict__ carry, int32_t W, int32_t R,         \
-      int32_t N, int32_t cpw, int32_t xcd_remap, int32_t scat_mode,                             \
-      const int32_t *__restrict__ hot_src, int32_t n_hot
-
-#define SHIRO_SPMM_ARGS(TIN, TOUT, a)                                                          \
-  (a).ptr, (a).idx, (a).vals, reinterpret_cast<const TIN*>((a).D), (a).ldd, (a).dot_out,      \
-      reinterpret_cast<const TIN*>((a).X), (a).ldx,                                            \
-      reinterpret_cast<TOUT*>((a).out), (a).ldo, reinterpret_cast<TOUT*>((a).scat), (a).lds,   \
-      (a).scat_idx, (a).chunk_row, (a).chunk_nz, (a).rid, (a).carry, (a).W, (a).R, (a).N,     \
-      (a).chunks_per_wave, (a).xcd_remap, (a).scat_mode, (a).hot_src, (a).n_hot
-
-#define SHIRO_SPMM_NAMES                                                                       \
-  ptr, idx, vals, D, ldd, dot_out, X, ldx, out, ldo, scat, lds, scat_idx, chunk_row, chunk_nz, rid, \
-      carry, W, R, N, cpw, xcd_remap, scat_mode, hot_src, n_hot
-
 template <typename TOUT, int VEC>
 __device__ __forceinline__ void epilogue_row(TOUT* __restrict__ out, int64_t ldo, TOUT* __restrict__ scat,
                                              int64_t lds, const int32_t* __restrict__ scat_idx,
@@ -169,15 +124,6 @@ __device__ __forceinline__ void epilogue_row(TOUT* __restrict__ out, int64_t ldo
     for (int e = 0; e < VEC; ++e) cur[e] += acc[e];
     Elem<TOUT>::template store<VEC>(o, cur);
   }
-}
-
-// Logical workgroup index: with xcd_remap, workgroups that the dispatcher
-// places on the same XCD (round robin over 8) get a contiguous index range,
-// so each XCD's L2 serves a contiguous range of rows.
-__device__ __forceinline__ int32_t logical_block(int32_t remap) {
-  const int32_t b = blockIdx.x, g = gridDim.x;
-  if (!remap || (g & 7)) return b;
-  return (b & 7) * (g >> 3) + (b >> 3);
 }
 
 // With DOT (one column tile only), each gathered row is also dotted with the
@@ -324,305 +270,9 @@ __global__ __launch_bounds__(kBlock) void k_spmm(SHIRO_SPMM_PARAMS(TIN, TOUT)) {
   }
 }
 
-// Variant for short rows: lane group g of a wavefront takes rows i0+g,
-// i0+g+G, ... of the chunk, UNROLL nonzeros per step, so a wavefront keeps G
-// rows in flight instead of one.  Each group reads the row pointers of its
-// next row at the start of the current one and that row's first indices
-// during the current row's last step, so a short row costs one dependent
-// round trip (its gathers).  Row bookkeeping is per group (vector
-// registers); groups diverge only in their trip counts.  Sums inside a row
-// keep a fixed order, so results stay reproducible.
-template <typename TIN, typename TOUT, int LANES, int VEC, int UNROLL, bool DOT, int SCAT>
-__global__ __launch_bounds__(kBlock) void k_spmm_grp(SHIRO_SPMM_PARAMS(TIN, TOUT)) {
-  constexpr int G = kWave / LANES;
-  const int lane = lane_id();
-  const int g = lane / LANES;
-  const int li = lane % LANES;
-  const int64_t c = (int64_t)blockIdx.y * (LANES * VEC) + (int64_t)li * VEC;
-  const bool cvalid = c < N;
-  const int64_t cl = cvalid ? c : 0;
-
-  const int32_t gw = uniform(logical_block(xcd_remap) * kWavesPerBlock + wave_id());
-  const int32_t w_begin = gw * cpw;
-  const int32_t w_end = min(w_begin + cpw, W);
-
-  for (int32_t w = w_begin; w < w_end; ++w) {
-    const int32_t i0 = chunk_row[w], i1 = chunk_row[w + 1];
-    const int64_t j0 = chunk_nz[w], j1 = chunk_nz[w + 1];
-    int32_t r = i0 + g;
-    if (r > i1 || r >= R) continue;
-    int64_t rs = ptr[r], re = ptr[r + 1];
-    int32_t xi[UNROLL];
-    float v[UNROLL];
-    bool ok[UNROLL];
-    bool have = false;
-    for (; r <= i1 && r < R; r += G) {
-      if (r == i1 && j1 <= rs) break;  // chunk holds nothing of row i1
-      const int64_t kb = rs > j0 ? rs : j0;
-      const int64_t ke = re < j1 ? re : j1;
-      const bool head = (r == i0) && (j0 > rs);
-      const bool tail = (r == i1);
-      const bool complete = !head && !tail;
-      const int32_t sidx = SCAT ? scat_idx[r] : 0;
-      // indices first, then the group's next row pointers, then the row's
-      // own dense rows (loads retire in issue order for the wait counter)
-      if (!have && kb < ke) {
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-          const int64_t kk = kb + u;
-          ok[u] = kk < ke;
-          const int64_t kc = ok[u] ? kk : ke - 1;
-          xi[u] = idx[kc];
-          v[u] = vals[kc];
-        }
-      }
-      have = false;
-      const int32_t rn = r + G;
-      const bool has_next = rn <= i1 && rn < R;
-      const int64_t rsn = has_next ? ptr[rn] : re;
-      const int64_t ren = has_next ? ptr[rn + 1] : re;
-      float pre[VEC];
-      if constexpr (SCAT == 1) {
-        if (complete) Elem<TOUT>::template load<VEC>(scat + (int64_t)sidx * lds + cl, pre);
-      }
-      float d[VEC];  // lanes past N read column 0; their dots are masked below
-      if constexpr (DOT) Elem<TIN>::template load<VEC>(D + (int64_t)r * ldd + cl, d);
-      float acc[VEC];
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
-      for (int64_t k = kb; k < ke; k += UNROLL) {
-        float x[UNROLL][VEC];
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u)
-          Elem<TIN>::template load<VEC>(X + (int64_t)xi[u] * ldx + cl, x[u]);
-        // next step of this row, or the first step of the group's next row
-        const bool same_row = k + UNROLL < ke;
-        const int64_t kbn = rsn > j0 ? rsn : j0;
-        const int64_t ken = ren < j1 ? ren : j1;
-        const bool next_nonempty = has_next && !(rn == i1 && j1 <= rsn) && kbn < ken;
-        const bool pf = same_row || next_nonempty;
-        const int64_t nb = same_row ? k + UNROLL : (next_nonempty ? kbn : kb);
-        const int64_t nl = same_row ? ke : (next_nonempty ? ken : ke);
-        int32_t xin[UNROLL];
-        float vn[UNROLL];
-        bool okn[UNROLL];
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-          const int64_t kk = nb + u;
-          okn[u] = pf && kk < nl;
-          const int64_t kc = kk < nl ? kk : nl - 1;
-          xin[u] = idx[kc];
-          vn[u] = vals[kc];
-        }
-        have = !same_row && next_nonempty;
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u)
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) {
-            const float t = fmaf(v[u], x[u][e], acc[e]);
-            acc[e] = ok[u] ? t : acc[e];
-          }
-        if constexpr (DOT) {
-#pragma unroll
-          for (int u = 0; u < UNROLL; ++u) {
-            float q = 0.f;
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) q = fmaf(d[e], x[u][e], q);
-            q = group_sum<LANES>(cvalid ? q : 0.f);
-            if (li == LANES - 1 && ok[u]) dot_out[k + u] = q;
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-          xi[u] = xin[u];
-          v[u] = vn[u];
-          ok[u] = okn[u];
-        }
-      }
-      if (cvalid) {
-        if (complete) {
-          if (out) Elem<TOUT>::template store<VEC>(out + (int64_t)r * ldo + c, acc);
-          if constexpr (SCAT == 1) {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) pre[e] += acc[e];
-            Elem<TOUT>::template store<VEC>(scat + (int64_t)sidx * lds + c, pre);
-          } else if constexpr (SCAT == 2) {
-            Elem<TOUT>::template store<VEC>(scat + (int64_t)sidx * lds + c, acc);
-          }
-        } else {
-          float* cs = carry + ((int64_t)w * 2 + (head ? 0 : 1)) * N + c;
-          Elem<float>::template store<VEC>(cs, acc);
-        }
-      }
-      rs = rsn;
-      re = ren;
-    }
-  }
-}
-
-// Nonzero walk.  Lane group g of a wavefront owns whole chunks and walks
-// their nonzeros UNROLL at a time without regard to row boundaries, so it
-// keeps UNROLL dense rows in flight whatever the row lengths (wave-per-row
-// and group-per-row kernels stall once per row, and the short rows of
-// power-law patterns dominate).  rid[k] is the row of nonzero k; a row's
-// sum is written when the walk reaches a nonzero of another row or the
-// chunk's end, and rows the walk steps over (no nonzeros) are written as
-// zeros.  Rows cut by the chunk's ends go to its carry slots as in k_spmm:
-// the first row's piece (empty or not) when that row began in an earlier
-// chunk, the last row's piece when the chunk holds any of it.  A group's
-// chunks are consecutive, so its nonzeros form one contiguous run and each
-// step's indices are loaded one step ahead, across chunk ends too.  Sums
-// inside a row keep pattern order, so results stay reproducible.  Rows
-// written once (the output, overwritten dB rows) and the dense rows D read
-// once are marked non-temporal, so they do not push the gathered rows out
-// of the caches (on the 2^24 R-MAT panel this took the transposed product
-// without dvals from 469 to 344 us).
-template <typename TIN, typename TOUT, int LANES, int VEC, int UNROLL, bool DOT, int SCAT>
-__global__ __launch_bounds__(kBlock) void k_spmm_flat(SHIRO_SPMM_PARAMS(TIN, TOUT)) {
-  constexpr int G = kWave / LANES;
-  const int lane = lane_id();
-  const int g = lane / LANES;
-  const int li = lane % LANES;
-  const int64_t c = (int64_t)blockIdx.y * (LANES * VEC) + (int64_t)li * VEC;
-  const bool cvalid = c < N;
-  const int64_t cl = cvalid ? c : 0;
-
-  const int64_t worker = (int64_t)uniform(logical_block(xcd_remap) * kWavesPerBlock + wave_id()) * G + g;
-  const int64_t wb = worker * cpw;
-  const int64_t we = wb + cpw < W ? wb + cpw : W;
-  if (wb >= we) return;  // whole lane groups leave; the others use no cross-group lane ops
-  const int64_t kend = chunk_nz[we];
-  int32_t xi[UNROLL], ri[UNROLL];
-  float v[UNROLL];
-  if (chunk_nz[wb] < kend) {
-#pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-      const int64_t kk = chunk_nz[wb] + u;
-      const int64_t kc = kk < kend ? kk : kend - 1;
-      xi[u] = idx[kc];
-      ri[u] = rid[kc];
-      v[u] = vals[kc];
-    }
-  }
-  for (int64_t w = wb; w < we; ++w) {
-    const int32_t i0 = chunk_row[w], i1 = chunk_row[w + 1];
-    const int64_t j0 = chunk_nz[w], j1 = chunk_nz[w + 1];
-    if (i0 >= R) break;
-    const bool has_head = j0 > ptr[i0];
-    // rows below row_end whose ends fall in this chunk are complete; `next`
-    // is the first of them not written yet
-    const int32_t row_end = i1 < R ? i1 : R;
-    int32_t next = has_head ? i0 + 1 : i0;
-    float* const head_slot = carry + (w * 2) * N + c;
-    float* const tail_slot = carry + (w * 2 + 1) * N + c;
-    if (has_head && ptr[i0 + 1] <= j0 && cvalid) {  // row i0 holds nothing here
-      float z[VEC];
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) z[e] = 0.f;
-      Elem<float>::template store<VEC>(head_slot, z);
-    }
-    // a complete row's sum: into the output, and into (or onto) its dB row
-    auto put = [&](int32_t r, int32_t sidx, const float(&a)[VEC], bool zero) {
-      if (out) Elem<TOUT>::template store_nt<VEC>(out + (int64_t)r * ldo + c, a);
-      if constexpr (SCAT == 1) {
-        if (!zero) {
-          float pre[VEC];
-          Elem<TOUT>::template load<VEC>(scat + (int64_t)sidx * lds + c, pre);
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) pre[e] += a[e];
-          Elem<TOUT>::template store<VEC>(scat + (int64_t)sidx * lds + c, pre);
-        }
-      } else if constexpr (SCAT == 2) {
-        Elem<TOUT>::template store_nt<VEC>(scat + (int64_t)sidx * lds + c, a);
-      }
-    };
-    // complete rows [next, lim) hold no nonzeros
-    auto zero_rows = [&](int32_t lim) {
-      for (; next < lim; ++next) {
-        if (!cvalid) continue;
-        float z[VEC];
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) z[e] = 0.f;
-        put(next, SCAT ? scat_idx[next] : 0, z, true);
-      }
-    };
-    int32_t cur = -1, scur = 0;  // open row and its scatter row
-    float acc[VEC];
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
-    auto flush = [&]() {
-      if (!cvalid) return;
-      if (cur == i0 && has_head) Elem<float>::template store<VEC>(head_slot, acc);
-      else if (cur == i1) Elem<float>::template store<VEC>(tail_slot, acc);
-      else put(cur, scur, acc, false);
-    };
-    for (int64_t k = j0; k < j1; k += UNROLL) {
-      bool ok[UNROLL];
-      float x[UNROLL][VEC];
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        ok[u] = k + u < j1;
-        Elem<TIN>::template load<VEC>(X + (int64_t)xi[u] * ldx + cl, x[u]);
-      }
-      float d[DOT ? UNROLL : 1][VEC];  // lanes past N read column 0; their dots are masked below
-      if constexpr (DOT) {
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) Elem<TIN>::template load_nt<VEC>(D + (int64_t)ri[u] * ldd + cl, d[u]);
-      }
-      int32_t sc[UNROLL];
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u) sc[u] = SCAT ? scat_idx[ri[u]] : 0;
-      // the next step: the rest of this chunk, else the next chunk's start
-      const int64_t kn = k + UNROLL < j1 ? k + UNROLL : j1;
-      int32_t xin[UNROLL], rin[UNROLL];
-      float vn[UNROLL];
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        const int64_t kk = kn + u;
-        const int64_t kc = kk < kend ? kk : kend - 1;
-        xin[u] = idx[kc];
-        rin[u] = rid[kc];
-        vn[u] = vals[kc];
-      }
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        if (ok[u] && ri[u] != cur) {
-          if (cur >= 0) flush();
-          zero_rows(ri[u]);
-          cur = ri[u];
-          scur = sc[u];
-          if (next <= cur) next = cur + 1;
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
-        }
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          const float t = fmaf(v[u], x[u][e], acc[e]);
-          acc[e] = ok[u] ? t : acc[e];
-        }
-        if constexpr (DOT) {
-          float q = 0.f;
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) q = fmaf(d[u][e], x[u][e], q);
-          q = group_sum<LANES>(cvalid ? q : 0.f);
-          if (li == LANES - 1 && ok[u]) dot_out[k + u] = q;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        xi[u] = xin[u];
-        ri[u] = rin[u];
-        v[u] = vn[u];
-      }
-    }
-    if (cur >= 0) flush();
-    zero_rows(row_end);
-  }
-}
-
-// Nonzero walk with windowed index streams.  Same walk, carries and output
-// order as k_spmm_flat, but a lane group no longer issues one vector load per
-// nonzero for each of its index, row-id and value streams: every LANES steps'
+// Nonzero walk of lane groups with windowed index streams.  Each lane group of
+// a wavefront walks its own chunks' nonzeros UNROLL at a time without regard
+// to row boundaries.  Its index, row-id and value streams: every LANES steps'
 // worth of those (a window of LANES consecutive nonzeros) come in with one
 // coalesced load per stream, lane li holding nonzero kw + li, and each step
 // takes its UNROLL slots from the window by lane permutes (ds_bpermute, the
@@ -1353,11 +1003,7 @@ int spmm_dispatch(const shiro_tuning_t& t, dim3 grid, hipStream_t s, const SpmmA
       else                                                                                             \
         k_spmm_win<TIN, TOUT, L, VEC, U, DOT, SCAT><<<grid, kBlock, lds_bytes, s>>>(                   \
             SHIRO_SPMM_ARGS(TIN, TOUT, a));                                                           \
-    } else if (t.group_rows == 2 && a.rid)                                                               \
-      k_spmm_flat<TIN, TOUT, L, VEC, U, DOT, SCAT><<<grid, kBlock, 0, s>>>(SHIRO_SPMM_ARGS(TIN, TOUT, a)); \
-    else if (t.group_rows)                                                                             \
-      k_spmm_grp<TIN, TOUT, L, VEC, U, DOT, SCAT><<<grid, kBlock, 0, s>>>(SHIRO_SPMM_ARGS(TIN, TOUT, a)); \
-    else                                                                                               \
+    } else                                                                                               \
       k_spmm<TIN, TOUT, L, VEC, U, DOT, SCAT><<<grid, kBlock, 0, s>>>(SHIRO_SPMM_ARGS(TIN, TOUT, a));     \
     SHIRO_LAUNCH_CHECK();                                                                              \
     return SHIRO_OK;                                                                                   \
@@ -1397,42 +1043,68 @@ int effective_lanes(int lanes, int32_t N, int vec) {
   return l;
 }
 
+// The walk holds row strides in 32 bits (bytes); rows further apart take the
+// row kernel.
+bool strides_32(const SpmmArgs& a, shiro_dtype in_dt, shiro_dtype out_dt) {
+  const int64_t in = in_dt == SHIRO_F32 ? 4 : 2, out = out_dt == SHIRO_F32 ? 4 : 2;
+  const int64_t lim = (int64_t)1 << 32;
+  return a.ldx * in < lim && a.ldd * in < lim && a.ldo * out < lim && a.lds * out < lim;
+}
+
 template <typename TIN, typename TOUT>
 int run_spmm_family(shiro_plan plan, shiro_tuning_t t, const WorkList* wl, SpmmArgs a, int vec,
                     hipStream_t s) {
-  t.lanes = effective_lanes(t.lanes, a.N, vec);
-  unsigned nb;
-  // the nonzero walk gives each lane group its own chunks
-  const int32_t workers = (t.group_rows >= 2 && a.rid) ? kWavesPerBlock * (kWave / t.lanes) : kWavesPerBlock;
-  SHIRO_TRY(grid_waves(plan, t, wl->W, workers, &a.chunks_per_wave, &nb));
-  const int ntiles = (int)ceil_div(a.N, (int64_t)t.lanes * vec);
-  a.xcd_remap = t.xcd_remap;
-  if (a.n_hot > 0 && (int64_t)a.n_hot * t.lanes * vec * (int64_t)sizeof(TIN) > 65536)
-    return set_error(SHIRO_ERR_UNSUPPORTED, "spmm: lds_rows rows of this width exceed 64 KB of LDS");
-  dim3 grid(nb, ntiles);
   constexpr int V16 = Elem<TIN>::kVec16;
   const bool store = a.scat_mode == 2;
-  if (a.dot_out) {
-    if (ntiles != 1) return set_error(SHIRO_ERR_UNSUPPORTED, "fused dvals needs one column tile");
-    if (a.scat && store) {
-      if (vec == V16) SHIRO_TRY((spmm_dispatch<TIN, TOUT, V16, true, 2>(t, grid, s, a)));
-      else SHIRO_TRY((spmm_dispatch<TIN, TOUT, 1, true, 2>(t, grid, s, a)));
-    } else if (a.scat) {
-      if (vec == V16) SHIRO_TRY((spmm_dispatch<TIN, TOUT, V16, true, 1>(t, grid, s, a)));
-      else SHIRO_TRY((spmm_dispatch<TIN, TOUT, 1, true, 1>(t, grid, s, a)));
-    } else {
-      if (vec == V16) SHIRO_TRY((spmm_dispatch<TIN, TOUT, V16, true, 0>(t, grid, s, a)));
-      else SHIRO_TRY((spmm_dispatch<TIN, TOUT, 1, true, 0>(t, grid, s, a)));
-    }
-  } else if (a.scat && store) {
-    if (vec == V16) SHIRO_TRY((spmm_dispatch<TIN, TOUT, V16, false, 2>(t, grid, s, a)));
-    else SHIRO_TRY((spmm_dispatch<TIN, TOUT, 1, false, 2>(t, grid, s, a)));
-  } else if (a.scat) {
-    if (vec == V16) SHIRO_TRY((spmm_dispatch<TIN, TOUT, V16, false, 1>(t, grid, s, a)));
-    else SHIRO_TRY((spmm_dispatch<TIN, TOUT, 1, false, 1>(t, grid, s, a)));
+  constexpr shiro_dtype in_dt = std::is_same<TIN, float>::value ? SHIRO_F32 : SHIRO_BF16;
+  constexpr shiro_dtype out_dt = std::is_same<TOUT, float>::value ? SHIRO_F32 : SHIRO_BF16;
+  unsigned nb;
+  if (is_walk(t) && a.rid && strides_32(a, in_dt, out_dt)) {
+    // one wavefront per chunk, all chunks in the grid: with a persistent grid
+    // of 16 workgroups per CU and runs of chunks per wavefront the 2^24 R-MAT
+    // panel's backward took 509 us instead of 470, its BF16 forward 194
+    // instead of 172, the ER panel's forward (N = 64) 268 instead of 240
+    const int wv = walk_vec(a.N, in_dt, t.lanes);
+    a.chunks_per_wave = (int32_t)ceil_div(wl->W, (int64_t)kWavesPerBlock << 23);  // below 2^32 threads
+    const int64_t waves = ceil_div(wl->W, (int64_t)a.chunks_per_wave);
+    const dim3 grid((unsigned)(ceil_div(ceil_div(waves, kWavesPerBlock), 8) * 8),
+                    (unsigned)ceil_div(a.N, (int64_t)kWave * wv));
+    a.xcd_remap = t.xcd_remap;
+    if (in_dt == SHIRO_F32) SHIRO_TRY(launch_walk_f32(a, wv, grid, s));
+    else if (out_dt == SHIRO_F32) SHIRO_TRY(launch_walk_bf16_f32(a, wv, grid, s));
+    else SHIRO_TRY(launch_walk_bf16(a, wv, grid, s));
   } else {
-    if (vec == V16) SHIRO_TRY((spmm_dispatch<TIN, TOUT, V16, false, 0>(t, grid, s, a)));
-    else SHIRO_TRY((spmm_dispatch<TIN, TOUT, 1, false, 0>(t, grid, s, a)));
+    t.lanes = effective_lanes(t.lanes, a.N, vec);
+    // the windowed walk gives each lane group its own chunks
+    const int32_t workers = (t.group_rows == 3 && a.rid) ? kWavesPerBlock * (kWave / t.lanes) : kWavesPerBlock;
+    SHIRO_TRY(grid_waves(plan, t, wl->W, workers, &a.chunks_per_wave, &nb));
+    const int ntiles = (int)ceil_div(a.N, (int64_t)t.lanes * vec);
+    a.xcd_remap = t.xcd_remap;
+    if (a.n_hot > 0 && (int64_t)a.n_hot * t.lanes * vec * (int64_t)sizeof(TIN) > 65536)
+      return set_error(SHIRO_ERR_UNSUPPORTED, "spmm: lds_rows rows of this width exceed 64 KB of LDS");
+    dim3 grid(nb, ntiles);
+    if (a.dot_out) {
+      if (ntiles != 1) return set_error(SHIRO_ERR_UNSUPPORTED, "fused dvals needs one column tile");
+      if (a.scat && store) {
+        if (vec == V16) SHIRO_TRY((spmm_dispatch<TIN, TOUT, V16, true, 2>(t, grid, s, a)));
+        else SHIRO_TRY((spmm_dispatch<TIN, TOUT, 1, true, 2>(t, grid, s, a)));
+      } else if (a.scat) {
+        if (vec == V16) SHIRO_TRY((spmm_dispatch<TIN, TOUT, V16, true, 1>(t, grid, s, a)));
+        else SHIRO_TRY((spmm_dispatch<TIN, TOUT, 1, true, 1>(t, grid, s, a)));
+      } else {
+        if (vec == V16) SHIRO_TRY((spmm_dispatch<TIN, TOUT, V16, true, 0>(t, grid, s, a)));
+        else SHIRO_TRY((spmm_dispatch<TIN, TOUT, 1, true, 0>(t, grid, s, a)));
+      }
+    } else if (a.scat && store) {
+      if (vec == V16) SHIRO_TRY((spmm_dispatch<TIN, TOUT, V16, false, 2>(t, grid, s, a)));
+      else SHIRO_TRY((spmm_dispatch<TIN, TOUT, 1, false, 2>(t, grid, s, a)));
+    } else if (a.scat) {
+      if (vec == V16) SHIRO_TRY((spmm_dispatch<TIN, TOUT, V16, false, 1>(t, grid, s, a)));
+      else SHIRO_TRY((spmm_dispatch<TIN, TOUT, 1, false, 1>(t, grid, s, a)));
+    } else {
+      if (vec == V16) SHIRO_TRY((spmm_dispatch<TIN, TOUT, V16, false, 0>(t, grid, s, a)));
+      else SHIRO_TRY((spmm_dispatch<TIN, TOUT, 1, false, 0>(t, grid, s, a)));
+    }
   }
   if (wl->nsplit == 0) return SHIRO_OK;
   const int fvec = (vec == V16 && (a.N % 4) == 0) ? 4 : 1;
@@ -1679,11 +1351,12 @@ namespace {
 // out[r] = sum vals[k] X[idx[k]] over a CSR-like pattern (ptr: R + 1) with
 // its work list, for the supported dtype pairs.
 int launch_pattern(shiro_plan plan, const shiro_tuning_t& t, const WorkList* wl, const int64_t* ptr,
-                   const int32_t* idx, const float* vals, int64_t R, const void* X, int64_t ldx,
+                   const int32_t* idx, const float* vals, int64_t R, const void* X, int64_t x_rows, int64_t ldx,
                    int32_t N, shiro_dtype in_dt, void* Y, int64_t ldy, shiro_dtype out_dt,
                    hipStream_t s, const int32_t* add_rows = nullptr, const int32_t* rid = nullptr,
                    float* carry = nullptr, const HotRows* hot = nullptr) {
   SpmmArgs a{};
+  a.x_rows = x_rows;
   if (hot) {  // the windowed walk reads the hot rows from LDS
     idx = hot->walk_idx;
     a.hot_src = hot->hot_src;
@@ -1805,15 +1478,15 @@ int launch_spmm(shiro_plan plan, const shiro_tuning_t& t, const float* vals, con
   if (plan->rows == 0 || N == 0) return SHIRO_OK;
   const WorkList* wl;
   SHIRO_TRY(ensure_rows_work(plan, t.chunk, !stream_capturing(s), s, &wl));
-  if (t.group_rows >= 2) SHIRO_TRY(ensure_row_rid(plan, !stream_capturing(s), s));
+  if (t.group_rows >= 1) SHIRO_TRY(ensure_row_rid(plan, !stream_capturing(s), s));
   SHIRO_TRY(ensure_carry(plan, (int64_t)wl->W * 2 * N, !stream_capturing(s)));
   const HotRows* hot = nullptr;
   if (t.group_rows == 3 && t.lds_rows > 0)
     SHIRO_TRY(ensure_hot(plan, SHIRO_KERNEL_SPMM, t.lds_rows, !stream_capturing(s), s, &hot));
   const float* v = plan_values(plan, vals, s);
   SHIRO_LAUNCH_CHECK();
-  return launch_pattern(plan, t, wl, plan->row_ptr, plan->colmap, v, plan->rows, X, ldx, N, in_dt, Y, ldy,
-                        out_dt, s, nullptr, t.group_rows >= 2 ? plan->row_rid : nullptr, nullptr, hot);
+  return launch_pattern(plan, t, wl, plan->row_ptr, plan->colmap, v, plan->rows, X, plan->U, ldx, N, in_dt, Y, ldy,
+                        out_dt, s, nullptr, t.group_rows >= 1 ? plan->row_rid : nullptr, nullptr, hot);
 }
 
 int launch_spmm_fixed(shiro_plan plan, const shiro_tuning_t& t, const float* vals, const void* X,
@@ -1821,7 +1494,7 @@ int launch_spmm_fixed(shiro_plan plan, const shiro_tuning_t& t, const float* val
                       float* carry, int64_t carry_cap, hipStream_t s) {
   if (plan->rows == 0 || N == 0) return SHIRO_OK;
   auto it = plan->rows_work.find(t.chunk);
-  if (it == plan->rows_work.end() || (t.group_rows >= 2 && !plan->row_rid))
+  if (it == plan->rows_work.end() || (t.group_rows >= 1 && !plan->row_rid))
     return set_error(SHIRO_ERR_NOT_READY,
                      "spmm_noalloc: work list of the tuning not built; run shiro_prepare for (N, dtype) first");
   const WorkList* wl = &it->second;
@@ -1839,8 +1512,8 @@ int launch_spmm_fixed(shiro_plan plan, const shiro_tuning_t& t, const float* val
   }
   const float* v = plan_values(plan, vals, s);
   SHIRO_LAUNCH_CHECK();
-  return launch_pattern(plan, t, wl, plan->row_ptr, plan->colmap, v, plan->rows, X, ldx, N, in_dt, Y, ldy,
-                        out_dt, s, nullptr, t.group_rows >= 2 ? plan->row_rid : nullptr, carry, hot);
+  return launch_pattern(plan, t, wl, plan->row_ptr, plan->colmap, v, plan->rows, X, plan->U, ldx, N, in_dt, Y, ldy,
+                        out_dt, s, nullptr, t.group_rows >= 1 ? plan->row_rid : nullptr, carry, hot);
 }
 
 int build_rowbased(shiro_plan plan, hipStream_t s) {
@@ -1904,7 +1577,7 @@ int launch_partial_c(shiro_plan plan, const shiro_tuning_t& t, const float* vals
   // values in block-major order (they may change from call to call)
   k_gather_vals<<<grid_for(plan->nnz), kBlock, 0, s>>>(rb.perm, vals + plan->nz_begin, plan->nnz, rb.vals);
   SHIRO_LAUNCH_CHECK();
-  return launch_pattern(plan, t, wl, rb.ptr, rb.col, rb.vals, rb.R, B, ldb, N, in_dt, Cp, ldc, out_dt, s,
+  return launch_pattern(plan, t, wl, rb.ptr, rb.col, rb.vals, rb.R, B, plan->n_cols, ldb, N, in_dt, Cp, ldc, out_dt, s,
                         nullptr, rb.rid);
 }
 
@@ -1917,17 +1590,24 @@ int launch_aggregate_c(shiro_plan plan, const shiro_tuning_t& t, const void* Cp,
   const WorkList* wa;
   SHIRO_TRY(ensure_rb_work(plan, 1, t.chunk, !cap, s, &wa));
   SHIRO_TRY(ensure_carry(plan, (int64_t)wa->W * 2 * N, !cap));
-  return launch_pattern(plan, t, wa, rb.agg_ptr, rb.agg_idx, rb.ones, plan->rows, Cp, ldc, N, in_dt, Y, ldy,
+  return launch_pattern(plan, t, wa, rb.agg_ptr, rb.agg_idx, rb.ones, plan->rows, Cp, rb.R, ldc, N, in_dt, Y, ldy,
                         out_dt, s, accumulate ? rb.iota : nullptr, rb.agg_rid);
 }
 
-int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& t, const float* vals, const void* dY,
+int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* vals, const void* dY,
                   int64_t lddy, int32_t N, shiro_dtype dt, void* dBp, int64_t lddbp, void* dB,
                   int64_t lddb, bool db_overwrite, const void* Bp, int64_t ldp, float* dvals,
                   bool* dvals_done, hipStream_t s) {
   if (dvals_done) *dvals_done = false;
   if (plan->U == 0 || N == 0 || (!dBp && !dB)) return SHIRO_OK;
   const bool cap = stream_capturing(s);
+  shiro_tuning_t t = tuned;
+  SpmmArgs a{};
+  a.ldx = lddy;
+  a.ldd = dvals && Bp ? ldp : 0;
+  a.ldo = dBp ? lddbp : 0;
+  a.lds = dB ? lddb : 0;
+  if (is_walk(t) && !strides_32(a, dt, dt)) t.group_rows = 0;
   if (!plan->tr.built) {
     if (cap) return set_error(SHIRO_ERR_CAPTURING, "backward: transposed pattern not prepared before capture");
     SHIRO_TRY(build_transposed(plan, s));
@@ -1944,7 +1624,6 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& t, const float* vals, c
   const HotRows* hot = nullptr;
   if (t.group_rows == 3 && t.lds_rows > 0)
     SHIRO_TRY(ensure_hot(plan, SHIRO_KERNEL_SPMM_T, t.lds_rows, !cap, s, &hot));
-  SpmmArgs a{};
   a.ptr = plan->tr.ptr;
   a.idx = hot ? hot->walk_idx : plan->tr.row;
   a.hot_src = hot ? hot->hot_src : nullptr;
@@ -1952,11 +1631,9 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& t, const float* vals, c
   a.rid = plan->tr.rid;
   a.vals = plan->tvals;
   a.X = dY;
-  a.ldx = lddy;
+  a.x_rows = plan->rows;
   a.out = dBp;
-  a.ldo = lddbp;
   a.scat = dB;
-  a.lds = lddb;
   a.scat_mode = db_overwrite ? 2 : 1;
   a.scat_idx = plan->unique_cols;
   a.chunk_row = wl->chunk_row;
@@ -1968,18 +1645,21 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& t, const float* vals, c
   int v;
   if (dt == SHIRO_F32) v = vec_for<float>(N, {{dY, lddy}, {dBp, lddbp}, {dB, lddb}, {Bp, ldp}});
   else v = vec_for<bf16_t>(N, {{dY, lddy}, {dBp, lddbp}, {dB, lddb}, {Bp, ldp}});
-  // dvals ride along when one column tile covers N
-  const bool fuse = dvals && Bp && (int64_t)effective_lanes(64, N, v) * v >= N;
+  // dvals ride along when one column tile covers N, or (the walk) up to four
+  // tiles, whose partial dots the scatter pass adds
+  const int tiles = is_walk(t) ? walk_dot_tiles(N, dt, t) : 1;
+  const bool fuse = dvals && Bp && (is_walk(t) ? tiles > 0 : (int64_t)effective_lanes(64, N, v) * v >= N);
   if (fuse) {
+    SHIRO_TRY(ensure_tdvals(plan, tiles, !cap));
     shiro_tuning_t tt = t;
-    tt.lanes = 64;  // one tile (effective lanes then cover N)
+    if (!is_walk(t)) tt.lanes = 64;  // one tile (effective lanes then cover N)
     a.D = Bp;
-    a.ldd = ldp;
     a.dot_out = plan->tdvals;
+    a.dot_ld = plan->nnz;
     if (dt == SHIRO_F32) SHIRO_TRY((run_spmm_family<float, float>(plan, tt, wl, a, v, s)));
     else SHIRO_TRY((run_spmm_family<bf16_t, bf16_t>(plan, tt, wl, a, v, s)));
-    k_scatter_vals<<<grid_for(plan->nnz), kBlock, 0, s>>>(plan->tr.perm, plan->tdvals, plan->nnz,
-                                                                     dvals + plan->nz_begin);
+    k_scatter_vals<<<grid_for(plan->nnz), kBlock, 0, s>>>(plan->tr.perm, plan->tdvals, tiles, plan->nnz,
+                                                          dvals + plan->nz_begin);
     SHIRO_LAUNCH_CHECK();
     if (dvals_done) *dvals_done = true;
     return SHIRO_OK;
@@ -2113,6 +1793,7 @@ int launch_spmm_per_block(shiro_plan plan, const float* vals, const void* X, int
     a.rid = pb.rid + n0;
     a.vals = plan->rb.vals + n0;
     a.X = X;
+    a.x_rows = plan->U;
     a.ldx = ldx;
     a.scat = acc;
     a.lds = lda;

@@ -1,0 +1,74 @@
+"""The nonzero walk at the edges of its tiles: widths around its 64-lane
+columns-per-lane steps, ragged and odd widths, rows that are no whole dwords
+(the 64-bit gather), chunks that cut rows into many pieces, hub and empty
+rows, several column tiles with their partial dots."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+# componentwise against |A||B|: float32 sums of at most a few hundred terms,
+# bfloat16 inputs and outputs rounded once each (2^-8 relative per rounding)
+TOL = {torch.float32: 1e-5, torch.bfloat16: 1e-2}
+
+
+@pytest.fixture(scope="module")
+def shiro():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2512_20178_amd as s
+
+    s._lib.load()
+    return s
+
+
+def _case(seed):
+    rng = np.random.default_rng(seed)
+    rows, cols = 150, 333
+    mask = rng.random((rows, cols)) < 0.04
+    mask[40, :] = rng.random(cols) < 0.8  # cut by many chunks
+    mask[60:75, :] = False  # empty rows inside a chunk
+    mask[-1, :] = False
+    vals = rng.uniform(0.1, 1, size=(rows, cols)).astype(np.float32) * mask
+    return synth.from_dense_pattern(vals, P=1, p=0, name="walk")
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("N", [1, 2, 31, 63, 64, 65, 127, 128, 129, 193, 257, 513])
+def test_walk_tile_edges(shiro, N, dtype):
+    A = _case(N)
+    dev = torch.device("cuda")
+    Ad, Ac = A.to(dev), oracle.Csr.from_synth(A)
+    plan = shiro.partition(Ad.row_ptr, Ad.col, A.n_rows, A.n_cols, 1, 0, check=True)
+    U, _ = shiro.select_rows(plan)
+    B = synth.dense(A.n_cols, N, N, synth.STREAM_B).to(dtype)
+    G = synth.dense(A.n_rows, N, N, synth.STREAM_DY).to(dtype)
+    Bn, Gn = B.float().numpy(), G.float().numpy()
+    tol = TOL[dtype]
+    Y0 = oracle.spmm(Ac, Bn, None), oracle.spmm(Ac, Bn, None, abs_mode=True)
+    uc, _, cm = oracle.select(Ac)
+    dB0 = oracle.spmm_t(Ac, Gn, cm, n_out=U), oracle.spmm_t(Ac, Gn, cm, n_out=U, abs_mode=True)
+    dv0 = oracle.sddmm(Ac, Gn, Bn, None), oracle.sddmm(Ac, Gn, Bn, None, abs_mode=True)
+    for chunk, lanes, pad in ((16, 64, 0), (100, 16, 1), (4096, 32, 3)):
+        for k in ("spmm", "spmm_t"):
+            shiro.set_tuning(plan, k, N, dtype, chunk=chunk, lanes=lanes, group_rows=2)
+        Bd = torch.zeros(A.n_cols, N + pad, dtype=dtype, device=dev)[:, :N].copy_(B)
+        Gd = torch.zeros(A.n_rows, N + pad, dtype=dtype, device=dev)[:, :N].copy_(G)
+        Bp = shiro.pack_B(plan, Bd, out=torch.empty(U, N + pad, dtype=dtype, device=dev)[:, :N])
+        Y = torch.full((A.n_rows, N + pad), float("nan"), dtype=dtype, device=dev)[:, :N]
+        shiro.spmm(plan, Ad.vals, Bp, out=Y)
+        assert oracle.rel_err(Y.float().cpu().numpy(), *Y0) <= tol, (chunk, lanes, pad)
+        dBp = torch.full((U, N + pad), float("nan"), dtype=dtype, device=dev)[:, :N]
+        dB = torch.ones(A.n_cols, N, dtype=dtype, device=dev)  # rows added to, every column once
+        dvals = torch.zeros(A.nnz, device=dev)
+        shiro.spmm_backward(plan, Ad.vals, Gd, Bp, dBpacked=dBp, dB=dB, dvals=dvals)
+        assert oracle.rel_err(dBp.float().cpu().numpy(), *dB0) <= tol, (chunk, lanes, pad)
+        full, fden = np.ones((A.n_cols, N)), np.ones((A.n_cols, N))
+        full[uc] += dB0[0]
+        fden[uc] += dB0[1]
+        assert oracle.rel_err(dB.float().cpu().numpy(), full, fden) <= tol, (chunk, lanes, pad)
+        assert oracle.rel_err(dvals.cpu().numpy(), *dv0) <= TOL[torch.float32], (chunk, lanes, pad)
