@@ -224,20 +224,63 @@ int ensure_tdvals(shiro_plan plan, int tiles, bool allocate) {
   return SHIRO_OK;
 }
 
-// Defaults from sweeps on MI355X (panel of a 2^24 R-MAT, N = 128): the
-// nonzero walk with four nonzeros in flight per lane group and chunks of 256
-// merge-path items for every kernel that has it; the sampled product keeps
-// its wavefront-per-row kernel with two in flight.
-shiro_tuning_t default_tuning(int kernel, int32_t, shiro_dtype) {
+// Rows, nonzeros and distinct gathered rows of the pattern a kernel walks
+// (0 rows where the structures are not built yet; every one is fixed by the
+// panel's pattern, so a plan's defaults do not change once they are).
+static void pattern_sizes(shiro_plan plan, int kernel, int64_t* rows, int64_t* nnz, int64_t* gathered) {
+  const int64_t U = std::max<int64_t>(plan->U, 0);
+  *rows = plan->rows;
+  *nnz = plan->nnz;
+  *gathered = U;
+  if (kernel == SHIRO_KERNEL_SPMM_T) {
+    *rows = U;
+    *gathered = plan->rows;
+  } else if (kernel == SHIRO_KERNEL_PARTIAL_C) {
+    *rows = plan->rb.built ? plan->rb.R : 0;
+  } else if (kernel == SHIRO_KERNEL_AGGREGATE_C) {
+    *nnz = *gathered = plan->rb.built ? plan->rb.R : 0;
+  }
+}
+
+// Defaults from sweeps on MI355X.  Every kernel that has it runs the nonzero
+// walk; the sampled product keeps its wavefront-per-row kernel with two in
+// flight.
+//
+// Chunk: at most 256 merge items (longer runs lengthen the serial sums and
+// the last round), fewer where that leaves the chip short of wavefronts: 256
+// CUs hold 8192 of them, and a chunk is a serial walk, so the aim is 16384
+// chunks, 16 items at least.  The 4096-vertex R-MAT (57K items, N = 32) took
+// 38 us backward at 256 and 28 at 16, 2^15 vertices (550K, N = 64) 58 at 256
+// and 43 at 32 to 64; from 2.2M items on 128 and 256 are alike.  Beyond that
+// no more chunks than leave the carry slots (2 N floats each) within the 32
+// MiB the allocation-free product has.
+//
+// Tile: 256 bytes of a row at a time (two passes over the index streams at
+// 512-byte rows) where rows are gathered many times from more than the caches
+// hold, because twice as many of them then stay in a 4 MB L2: 2^21 GCN matrix
+// at N = 128 forward 6.45 -> 5.93 ms, backward 12.7 -> 11.8; 2^18 R-MAT (15
+// nonzeros a row) 188 -> 169 and 356 -> 328 us.  Otherwise 512: with few uses
+// per row (2^24 panel, 3.4) or short rows (its backward, 3.4 nonzeros, 471
+// against 496 us) or cached matrices (2^16 R-MAT, 1M nonzeros, 47 against 51)
+// a second pass costs more than it saves.
+shiro_tuning_t default_tuning(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt) {
   const bool walk = kernel != SHIRO_KERNEL_SDDMM;
   shiro_tuning_t t;
   t.chunk = walk ? 256 : 128;
-  t.lanes = 64;
+  t.lanes = walk ? 32 : 64;
   t.unroll = walk ? 4 : 2;
   t.group_rows = walk ? 2 : 0;
   t.xcd_remap = 0;
   t.wg_per_cu = walk ? 16 : 8;
   t.lds_rows = 0;
+  if (!walk) return t;
+  int64_t rows, nnz, gathered;
+  pattern_sizes(plan, kernel, &rows, &nnz, &gathered);
+  const int64_t chunks = std::min<int64_t>(16384, (1 << 22) / std::max(N, 1));
+  const int64_t c = ceil_div(rows + nnz, std::max<int64_t>(chunks, 1));
+  t.chunk = (int32_t)std::min<int64_t>(256, std::max<int64_t>(16, ceil_div(c, 16) * 16));
+  if (nnz >= (1 << 21) && nnz >= 12 * rows && nnz >= 12 * gathered) t.lanes = 16;
+  (void)dt;
   return t;
 }
 
@@ -275,7 +318,7 @@ int validate_tuning(int kernel, int32_t N, shiro_dtype dt, const shiro_tuning_t&
 shiro_tuning_t tuning_for(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt) {
   auto it = plan->tuning.find(TuneKey{kernel, N, (int)dt});
   if (it != plan->tuning.end()) return it->second;
-  return default_tuning(kernel, N, dt);
+  return default_tuning(plan, kernel, N, dt);
 }
 
 static bool env_check() {
@@ -485,7 +528,7 @@ static int tune_one(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt, Tune
       return launch_aggregate_c(plan, t, b.Cp, N, N, dt, b.Y, N, dt, false, s);
     return launch_sddmm(plan, t, b.vals, b.dY, N, b.Bp, N, N, dt, b.dvals, s);
   };
-  shiro_tuning_t best = default_tuning(kernel, N, dt);
+  shiro_tuning_t best = default_tuning(plan, kernel, N, dt);
   float best_ms = 1e30f;
   auto consider = [&](shiro_tuning_t t, float* ms_out = nullptr) -> int {
     float ms;
@@ -501,7 +544,7 @@ static int tune_one(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt, Tune
   // stage 1: work size and depth
   for (int chunk : {128, 256, 512, 1024, 2048})
     for (int unroll : {1, 2, 4}) {
-      shiro_tuning_t t = default_tuning(kernel, N, dt);
+      shiro_tuning_t t = default_tuning(plan, kernel, N, dt);
       t.chunk = chunk;
       t.unroll = unroll;
       SHIRO_TRY(consider(t));

@@ -308,7 +308,7 @@ inline int walk_dot_tiles(int32_t N, shiro_dtype dt, const shiro_tuning_t& t) {
   return n <= 4 ? (int)n : 0;
 }
 
-shiro_tuning_t default_tuning(int kernel, int32_t N, shiro_dtype dt);
+shiro_tuning_t default_tuning(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt);
 // The tuning a plan uses for one kernel family (its own, else the default).
 shiro_tuning_t tuning_for(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt);
 int validate_tuning(int kernel, int32_t N, shiro_dtype dt, const shiro_tuning_t& t);

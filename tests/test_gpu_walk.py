@@ -72,3 +72,24 @@ def test_walk_tile_edges(shiro, N, dtype):
         fden[uc] += dB0[1]
         assert oracle.rel_err(dB.float().cpu().numpy(), full, fden) <= tol, (chunk, lanes, pad)
         assert oracle.rel_err(dvals.cpu().numpy(), *dv0) <= TOL[torch.float32], (chunk, lanes, pad)
+
+
+@pytest.mark.parametrize("N", [1, 32, 256, 1024])
+def test_default_chunks(shiro, N):
+    """Default chunks: 16 to 256 items, at most 16384 chunks unless they have
+    256 items, and no more carry slots than the allocation-free product holds
+    where 256-item chunks fit it; the product through it equals spmm."""
+    A = synth.small_rmat(13, 16)
+    dev = torch.device("cuda")
+    Ad = A.to(dev)
+    plan = shiro.partition(Ad.row_ptr, Ad.col, A.n_rows, A.n_cols, 1, 0)
+    U, _ = shiro.select_rows(plan)
+    items = A.n_rows + A.nnz
+    for k in ("spmm", "spmm_t"):
+        c = shiro.get_tuning(plan, k, N)["chunk"]
+        n = -(-(items if k == "spmm" else U + A.nnz) // c)
+        assert 16 <= c <= 256 and (c == 256 or (n <= 16384 and 2 * n * N * 4 <= 32 << 20))
+    shiro.prepare(plan, N, ops=("spmm",))
+    Bp = synth.dense(U, N, 0, synth.STREAM_B).to(dev)
+    out = torch.empty(A.n_rows, N, device=dev)
+    assert torch.equal(shiro.spmm_noalloc(plan, Ad.vals, Bp, out), shiro.spmm(plan, Ad.vals, Bp))
