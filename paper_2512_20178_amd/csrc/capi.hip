@@ -357,6 +357,8 @@ static void plan_free(shiro_plan plan) {
   dev_free(plan->tr.row);
   dev_free(plan->tr.perm);
   dev_free(plan->tr.rid);
+  dev_free(plan->tr.stage_of_csr);
+  dev_free(plan->tr.entry_of_stage);
   dev_free(plan->seg.seg_row);
   dev_free(plan->seg.seg_begin);
   dev_free(plan->seg.seg_end);
@@ -1015,7 +1017,7 @@ SHIRO_API int shiro_prepare(shiro_plan plan, int32_t N, shiro_dtype dt, uint32_t
     SHIRO_TRY(build_transposed(plan, s));
     SHIRO_TRY(ensure_tvals(plan, true));
     const shiro_tuning_t t = tuning_for(plan, SHIRO_KERNEL_SPMM_T, N, dt);
-    SHIRO_TRY(ensure_tdvals(plan, is_walk(t) ? walk_dot_tiles(N, dt, t) : 1, true));
+    SHIRO_TRY(ensure_tdvals(plan, is_walk(t) ? std::max(walk_dot_tiles(N, dt, t), 1) : 1, true));
     SHIRO_TRY(ensure_cols_work(plan, t.chunk, true, s, &wl));
     SHIRO_TRY(ensure_carry(plan, (int64_t)wl->W * 2 * N, true));
     const HotRows* hot;

@@ -35,6 +35,11 @@ struct Transposed {
   int32_t* row = nullptr;   // nnz: panel row of each entry
   int32_t* perm = nullptr;  // nnz: CSR position of each entry (value index)
   int32_t* rid = nullptr;   // nnz: transposed row (packed column) of each entry
+  // Large patterns permute their values in two passes through a staged order
+  // (permute.hip) instead of through perm, which is then not kept: place in
+  // the staged order of each CSR position, and transposed entry of each place.
+  int32_t* stage_of_csr = nullptr;  // nnz, or NULL
+  int32_t* entry_of_stage = nullptr;  // nnz, or NULL
 };
 
 // Per-block row segments for the one-launch-per-block mode.
@@ -213,6 +218,16 @@ int run_select(shiro_plan plan, hipStream_t s, bool sync);
 int64_t sort_scratch_bytes(int64_t n);
 int radix_sort_pairs(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* keys_out,
                      uint32_t* vals_out, int64_t n, int key_bits, void* scratch, hipStream_t s);
+
+// ---- permute.hip ------------------------------------------------------------
+// out[k] = vals[map[k]].
+int gather_values(const int32_t* map, const float* vals, int64_t n, float* out, hipStream_t s);
+// Values between CSR order and transposed order (plan->tr).
+int build_value_permutation(shiro_plan plan, hipStream_t s);
+// tvals[j] = vals[perm[j]]; stage: nnz floats of scratch.
+int values_to_transposed(shiro_plan plan, const float* vals, float* tvals, float* stage, hipStream_t s);
+// vals[perm[j]] = sum over the sets t < sets of tvals[j + t nnz].
+int values_from_transposed(shiro_plan plan, const float* tvals, int sets, float* vals, float* stage, hipStream_t s);
 
 // ---- spmm.hip ---------------------------------------------------------------
 int build_worklist(const int64_t* ptr, int64_t R, int64_t nnz, int32_t chunk, WorkList* wl,

@@ -83,28 +83,6 @@ __global__ void k_split_emit(const int32_t* __restrict__ flag, const int64_t* __
   split[3 * s + 2] = r;
 }
 
-__global__ void k_gather_vals(const int32_t* __restrict__ perm, const float* __restrict__ vals,
-                              int64_t nnz, float* __restrict__ out) {
-  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz;
-       j += (int64_t)gridDim.x * blockDim.x)
-    out[j] = vals[perm[j]];
-}
-
-// in: one set of partial dots per column tile, n apart.
-//
-// One value per thread: with four per thread (16-byte index loads) the
-// scattered stores ran slower on the MI355X (55 against 44 us for 4.2M
-// values), as did a gather through the inverse permutation.
-__global__ void k_scatter_vals(const int32_t* __restrict__ perm, const float* __restrict__ in, int tiles,
-                               int64_t n, float* __restrict__ out) {
-  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n;
-       j += (int64_t)gridDim.x * blockDim.x) {
-    float s = in[j];
-    for (int t = 1; t < tiles; ++t) s += in[j + t * n];
-    out[perm[j]] = s;
-  }
-}
-
 // ---------------------------------------------------------------------------
 // SpMM: out[r, :] = sum_{k in row r} vals[k] * X[idx[k], :]
 // ---------------------------------------------------------------------------
@@ -1230,6 +1208,7 @@ int build_transposed(shiro_plan plan, hipStream_t s) {
   // subset plans read the caller's values through the value map
   if (plan->vmap) SHIRO_TRY(launch_compose(tr.perm, plan->vmap, nnz, s));
   SHIRO_HIP(hipStreamSynchronize(s));
+  SHIRO_TRY(build_value_permutation(plan, s));
   tr.built = true;
   return SHIRO_OK;
 }
@@ -1404,7 +1383,7 @@ int launch_pattern(shiro_plan plan, const shiro_tuning_t& t, const WorkList* wl,
 static const float* plan_values(shiro_plan plan, const float* vals, hipStream_t s) {
   const float* v = vals + plan->nz_begin;
   if (!plan->vmap || plan->nnz == 0) return v;
-  k_gather_vals<<<grid_for(plan->nnz), kBlock, 0, s>>>(plan->vmap, v, plan->nnz, plan->svals);
+  (void)gather_values(plan->vmap, v, plan->nnz, plan->svals, s);  // the caller checks the launch
   return plan->svals;
 }
 
@@ -1575,8 +1554,7 @@ int launch_partial_c(shiro_plan plan, const shiro_tuning_t& t, const float* vals
   SHIRO_TRY(ensure_rb_work(plan, 0, t.chunk, !cap, s, &wl));
   SHIRO_TRY(ensure_carry(plan, (int64_t)wl->W * 2 * N, !cap));
   // values in block-major order (they may change from call to call)
-  k_gather_vals<<<grid_for(plan->nnz), kBlock, 0, s>>>(rb.perm, vals + plan->nz_begin, plan->nnz, rb.vals);
-  SHIRO_LAUNCH_CHECK();
+  SHIRO_TRY(gather_values(rb.perm, vals + plan->nz_begin, plan->nnz, rb.vals, s));
   return launch_pattern(plan, t, wl, rb.ptr, rb.col, rb.vals, rb.R, B, plan->n_cols, ldb, N, in_dt, Cp, ldc, out_dt, s,
                         nullptr, rb.rid);
 }
@@ -1618,9 +1596,9 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* val
   SHIRO_TRY(ensure_tvals(plan, !cap));
   // values in transposed order: one streaming gather per call, so the hot
   // loop reads them contiguously instead of through a dependent index
-  k_gather_vals<<<grid_for(plan->nnz), kBlock, 0, s>>>(plan->tr.perm, vals + plan->nz_begin, plan->nnz,
-                                                        plan->tvals);
-  SHIRO_LAUNCH_CHECK();
+  // (the dots' buffer is free until the walk and serves as staging area)
+  if (plan->tr.stage_of_csr) SHIRO_TRY(ensure_tdvals(plan, 1, !cap));
+  SHIRO_TRY(values_to_transposed(plan, vals + plan->nz_begin, plan->tvals, plan->tdvals, s));
   const HotRows* hot = nullptr;
   if (t.group_rows == 3 && t.lds_rows > 0)
     SHIRO_TRY(ensure_hot(plan, SHIRO_KERNEL_SPMM_T, t.lds_rows, !cap, s, &hot));
@@ -1658,9 +1636,7 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* val
     a.dot_ld = plan->nnz;
     if (dt == SHIRO_F32) SHIRO_TRY((run_spmm_family<float, float>(plan, tt, wl, a, v, s)));
     else SHIRO_TRY((run_spmm_family<bf16_t, bf16_t>(plan, tt, wl, a, v, s)));
-    k_scatter_vals<<<grid_for(plan->nnz), kBlock, 0, s>>>(plan->tr.perm, plan->tdvals, tiles, plan->nnz,
-                                                          dvals + plan->nz_begin);
-    SHIRO_LAUNCH_CHECK();
+    SHIRO_TRY(values_from_transposed(plan, plan->tdvals, tiles, dvals + plan->nz_begin, plan->tvals, s));
     if (dvals_done) *dvals_done = true;
     return SHIRO_OK;
   }
@@ -1775,9 +1751,7 @@ int launch_spmm_per_block(shiro_plan plan, const float* vals, const void* X, int
   SHIRO_LAUNCH_CHECK();
   if (plan->nnz > 0) {
     // values in block-major order (they may change from call to call)
-    k_gather_vals<<<grid_for(plan->nnz), kBlock, 0, s>>>(plan->rb.perm, vals + plan->nz_begin, plan->nnz,
-                                                          plan->rb.vals);
-    SHIRO_LAUNCH_CHECK();
+    SHIRO_TRY(gather_values(plan->rb.perm, vals + plan->nz_begin, plan->nnz, plan->rb.vals, s));
   }
   shiro_tuning_t t = tuning_for(plan, SHIRO_KERNEL_SPMM, N, in_dt);
   if (t.group_rows < 2) t.group_rows = 2;  // the walk: every block's entries are non-empty rows

@@ -93,3 +93,34 @@ def test_default_chunks(shiro, N):
     Bp = synth.dense(U, N, 0, synth.STREAM_B).to(dev)
     out = torch.empty(A.n_rows, N, device=dev)
     assert torch.equal(shiro.spmm_noalloc(plan, Ad.vals, Bp, out), shiro.spmm(plan, Ad.vals, Bp))
+
+
+@pytest.mark.parametrize("n_rows", [1 << 19, 1 << 18])
+def test_staged_value_permutation(shiro, n_rows):
+    """Values in and gradients out of the transposed order through the staged
+    order of large patterns (13M nonzeros; the smaller pattern, 6.5M, keeps the
+    direct permutation).  One nonzero value per row and column id makes every
+    moved value visible: dB[c] = sum of the values of column c, dvals[k] = the
+    product of two small integers, both exact in float32."""
+    dev = torch.device("cuda")
+    deg = 25
+    g = torch.Generator(device=dev)
+    g.manual_seed(n_rows)
+    # deg distinct columns per row, ascending
+    step = n_rows // deg
+    col = torch.randint(step, (n_rows, deg), generator=g, device=dev) + torch.arange(deg, device=dev) * step
+    row_ptr = torch.arange(0, n_rows * deg + 1, deg, device=dev)
+    vals = torch.randint(-3, 4, (n_rows * deg,), generator=g, device=dev).float()
+    plan = shiro.partition(row_ptr, col.reshape(-1).int(), n_rows, n_rows, 1, 0)
+    U, _ = shiro.select_rows(plan)
+    G = torch.randint(-2, 3, (n_rows, 1), generator=g, device=dev).float()
+    B = torch.randint(-2, 3, (n_rows, 1), generator=g, device=dev).float()
+    Bp = shiro.pack_B(plan, B)
+    dB = torch.zeros_like(B)
+    dvals = torch.full_like(vals, float("nan"))
+    shiro.spmm_backward(plan, vals, G, Bp, dB=dB, dvals=dvals, dB_overwrite=True)
+    rows = torch.arange(n_rows, device=dev).repeat_interleave(deg)
+    want = torch.zeros(n_rows, dtype=torch.float64, device=dev)
+    want.index_add_(0, col.reshape(-1), (vals * G[rows, 0]).double())
+    assert torch.equal(dB[:, 0].double(), want)
+    assert torch.equal(dvals, G[rows, 0] * B[col.reshape(-1), 0])
