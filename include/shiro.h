@@ -143,7 +143,8 @@ typedef struct {
                       * nonzeros; 1 or 2: the nonzero walk, a wavefront per
                       * chunk, every lane on every gathered row; 3: the windowed
                       * walk, each lane group of a wavefront on its own chunks.
-                      * Sampled product (SHIRO_KERNEL_SDDMM): 0 or 1            */
+                      * Sampled product (SHIRO_KERNEL_SDDMM): 0 or 1, the walk
+                      * either way                                              */
   int32_t xcd_remap; /* 1: give each XCD a contiguous range of work            */
   int32_t wg_per_cu; /* persistent grid: workgroups per compute unit (not the
                       * nonzero walk, whose grid holds every chunk)             */

@@ -242,9 +242,8 @@ static void pattern_sizes(shiro_plan plan, int kernel, int64_t* rows, int64_t* n
   }
 }
 
-// Defaults from sweeps on MI355X.  Every kernel that has it runs the nonzero
-// walk; the sampled product keeps its wavefront-per-row kernel with two in
-// flight.
+// Defaults from sweeps on MI355X: the nonzero walk for every kernel (the
+// sampled product has no other).
 //
 // Chunk: at most 256 merge items (longer runs lengthen the serial sums and
 // the last round), fewer where that leaves the chip short of wavefronts: 256
@@ -263,24 +262,20 @@ static void pattern_sizes(shiro_plan plan, int kernel, int64_t* rows, int64_t* n
 // per row (2^24 panel, 3.4) or short rows (its backward, 3.4 nonzeros, 471
 // against 496 us) or cached matrices (2^16 R-MAT, 1M nonzeros, 47 against 51)
 // a second pass costs more than it saves.
-shiro_tuning_t default_tuning(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt) {
-  const bool walk = kernel != SHIRO_KERNEL_SDDMM;
+shiro_tuning_t default_tuning(shiro_plan plan, int kernel, int32_t N, shiro_dtype) {
   shiro_tuning_t t;
-  t.chunk = walk ? 256 : 128;
-  t.lanes = walk ? 32 : 64;
-  t.unroll = walk ? 4 : 2;
-  t.group_rows = walk ? 2 : 0;
+  t.lanes = 32;
+  t.unroll = 4;
+  t.group_rows = kernel == SHIRO_KERNEL_SDDMM ? 1 : 2;
   t.xcd_remap = 0;
-  t.wg_per_cu = walk ? 16 : 8;
+  t.wg_per_cu = 16;
   t.lds_rows = 0;
-  if (!walk) return t;
   int64_t rows, nnz, gathered;
   pattern_sizes(plan, kernel, &rows, &nnz, &gathered);
   const int64_t chunks = std::min<int64_t>(16384, (1 << 22) / std::max(N, 1));
   const int64_t c = ceil_div(rows + nnz, std::max<int64_t>(chunks, 1));
   t.chunk = (int32_t)std::min<int64_t>(256, std::max<int64_t>(16, ceil_div(c, 16) * 16));
   if (nnz >= (1 << 21) && nnz >= 12 * rows && nnz >= 12 * gathered) t.lanes = 16;
-  (void)dt;
   return t;
 }
 
@@ -562,7 +557,9 @@ static int tune_one(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt, Tune
     for (int lanes : {64, 32, 16})
       for (int wg : {2, 4, 8, 16})
         for (int xcd : {0, 1}) {
-          if (walk && (grp == 1 || (grp == 2 && (wg != 16 || lanes == 64)))) continue;  // the same launch as another candidate
+          // the same launch as another candidate
+          const bool is_w = !walk || grp == 1 || grp == 2;
+          if (is_w && (wg != 16 || lanes == 64 || grp != (walk ? 2 : 1))) continue;
           shiro_tuning_t t = base;
           t.group_rows = grp;
           t.lanes = lanes;
@@ -1024,6 +1021,8 @@ SHIRO_API int shiro_prepare(shiro_plan plan, int32_t N, shiro_dtype dt, uint32_t
     if (t.group_rows == 3 && t.lds_rows > 0) SHIRO_TRY(ensure_hot(plan, SHIRO_KERNEL_SPMM_T, t.lds_rows, true, s, &hot));
     const shiro_tuning_t t2 = tuning_for(plan, SHIRO_KERNEL_SDDMM, N, dt);
     SHIRO_TRY(ensure_rows_work(plan, t2.chunk, true, s, &wl));
+    SHIRO_TRY(ensure_row_rid(plan, true, s));
+    SHIRO_TRY(ensure_tdvals(plan, walk_dot_tiles(N, dt, t2), true));
   }
   if (ops & SHIRO_OP_ROW_BASED) {
     SHIRO_TRY(build_rowbased(plan, s));

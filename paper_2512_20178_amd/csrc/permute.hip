@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kBlock) void k_scatter_vals(const int32_t* __restri
   for (int64_t j = blockIdx.x * (int64_t)kBlock + threadIdx.x; j < n; j += (int64_t)gridDim.x * kBlock) {
     float s = in[j];
     for (int t = 1; t < sets; ++t) s += in[j + t * n];
-    out[perm[j]] = s;
+    out[perm ? (int64_t)perm[j] : j] = s;
   }
 }
 
@@ -184,6 +184,13 @@ int gather_values(const int32_t* map, const float* vals, int64_t n, float* out, 
   return SHIRO_OK;
 }
 
+int scatter_values(const int32_t* map, const float* in, int sets, int64_t n, float* out, hipStream_t s) {
+  if (n <= 0) return SHIRO_OK;
+  k_scatter_vals<<<grid_for(n), kBlock, 0, s>>>(map, in, sets, n, out);
+  SHIRO_LAUNCH_CHECK();
+  return SHIRO_OK;
+}
+
 int values_to_transposed(shiro_plan plan, const float* vals, float* tvals, float* stage, hipStream_t s) {
   const Transposed& tr = plan->tr;
   const int64_t n = plan->nnz;
@@ -198,12 +205,7 @@ int values_to_transposed(shiro_plan plan, const float* vals, float* tvals, float
 int values_from_transposed(shiro_plan plan, const float* tvals, int sets, float* vals, float* stage, hipStream_t s) {
   const Transposed& tr = plan->tr;
   const int64_t n = plan->nnz;
-  if (n <= 0) return SHIRO_OK;
-  if (!tr.stage_of_csr) {
-    k_scatter_vals<<<grid_for(n), kBlock, 0, s>>>(tr.perm, tvals, sets, n, vals);
-    SHIRO_LAUNCH_CHECK();
-    return SHIRO_OK;
-  }
+  if (!tr.stage_of_csr) return scatter_values(tr.perm, tvals, sets, n, vals, s);
   k_stage_window<true><<<window_blocks(n), kBlock, 0, s>>>(tr.entry_of_stage, tvals, sets, n, stage);
   SHIRO_LAUNCH_CHECK();
   k_stage_runs<true><<<(unsigned)ceil_div(n, kRun), kBlock, 0, s>>>(tr.stage_of_csr, stage, n, vals);

@@ -222,6 +222,8 @@ int radix_sort_pairs(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t*
 // ---- permute.hip ------------------------------------------------------------
 // out[k] = vals[map[k]].
 int gather_values(const int32_t* map, const float* vals, int64_t n, float* out, hipStream_t s);
+// out[map ? map[k] : k] = sum over the sets t < sets of in[k + t n].
+int scatter_values(const int32_t* map, const float* in, int sets, int64_t n, float* out, hipStream_t s);
 // Values between CSR order and transposed order (plan->tr).
 int build_value_permutation(shiro_plan plan, hipStream_t s);
 // tvals[j] = vals[perm[j]]; stage: nnz floats of scratch.

@@ -995,22 +995,15 @@ int spmm_dispatch(const shiro_tuning_t& t, dim3 grid, hipStream_t s, const SpmmA
 }
 
 template <typename TIN, int VEC>
-int sddmm_dispatch(const shiro_tuning_t& t, dim3 grid, hipStream_t s, const SddmmArgs& a) {
-#define SHIRO_SDDMM_CASE(L, U)                                                              \
-  if (t.lanes == L && t.unroll == U) {                                                      \
-    k_sddmm<TIN, L, VEC, U><<<grid, kBlock, 0, s>>>(                                        \
-        a.ptr, a.idx, reinterpret_cast<const TIN*>(a.dY), a.lddy,                           \
-        reinterpret_cast<const TIN*>(a.Bp), a.ldp, a.dvals, a.out_map, a.chunk_row,         \
-        a.chunk_nz, a.W, a.R, a.N, a.chunks_per_wave, a.xcd_remap);                         \
-    SHIRO_LAUNCH_CHECK();                                                                   \
-    return SHIRO_OK;                                                                        \
-  }
-  SHIRO_SDDMM_CASE(8, 1) SHIRO_SDDMM_CASE(8, 2) SHIRO_SDDMM_CASE(8, 4)
-  SHIRO_SDDMM_CASE(16, 1) SHIRO_SDDMM_CASE(16, 2) SHIRO_SDDMM_CASE(16, 4)
-  SHIRO_SDDMM_CASE(32, 1) SHIRO_SDDMM_CASE(32, 2) SHIRO_SDDMM_CASE(32, 4)
-  SHIRO_SDDMM_CASE(64, 1) SHIRO_SDDMM_CASE(64, 2) SHIRO_SDDMM_CASE(64, 4)
-#undef SHIRO_SDDMM_CASE
-  return set_error(SHIRO_ERR_UNSUPPORTED, "sddmm: no kernel for lanes/unroll");
+int run_sddmm(shiro_plan plan, const WorkList* wl, SddmmArgs a, hipStream_t s) {
+  shiro_tuning_t t = default_tuning(plan, SHIRO_KERNEL_SDDMM, a.N, SHIRO_F32);
+  unsigned nb;
+  SHIRO_TRY(grid_waves(plan, t, wl->W, kWavesPerBlock, &a.chunks_per_wave, &nb));
+  k_sddmm<TIN, 64, VEC, 2><<<dim3(nb), kBlock, 0, s>>>(
+      a.ptr, a.idx, reinterpret_cast<const TIN*>(a.dY), a.lddy, reinterpret_cast<const TIN*>(a.Bp), a.ldp, a.dvals,
+      a.out_map, a.chunk_row, a.chunk_nz, a.W, a.R, a.N, a.chunks_per_wave, 0);
+  SHIRO_LAUNCH_CHECK();
+  return SHIRO_OK;
 }
 
 // Lanes actually used: never more than one column tile needs.
@@ -1019,6 +1012,23 @@ int effective_lanes(int lanes, int32_t N, int vec) {
   int l = lanes;
   while (l > 8 && l / 2 >= need) l /= 2;
   return l;
+}
+
+// The walk over a.W chunks: one wavefront per chunk, all chunks in the grid.
+// With a persistent grid of 16 workgroups per CU and runs of chunks per
+// wavefront the 2^24 R-MAT panel's backward took 509 us instead of 470, its
+// BF16 forward 194 instead of 172, the ER panel's forward (N = 64) 268
+// instead of 240.
+int run_walk(const shiro_tuning_t& t, shiro_dtype in_dt, shiro_dtype out_dt, SpmmArgs& a, hipStream_t s) {
+  const int vec = walk_vec(a.N, in_dt, t.lanes);
+  a.chunks_per_wave = (int32_t)ceil_div(a.W, (int64_t)kWavesPerBlock << 23);  // below 2^32 threads
+  const int64_t waves = ceil_div(a.W, (int64_t)a.chunks_per_wave);
+  const dim3 grid((unsigned)(ceil_div(ceil_div(waves, kWavesPerBlock), 8) * 8),
+                  (unsigned)ceil_div(a.N, (int64_t)kWave * vec));
+  a.xcd_remap = t.xcd_remap;
+  if (in_dt == SHIRO_F32) return launch_walk_f32(a, vec, grid, s);
+  if (out_dt == SHIRO_F32) return launch_walk_bf16_f32(a, vec, grid, s);
+  return launch_walk_bf16(a, vec, grid, s);
 }
 
 // The walk holds row strides in 32 bits (bytes); rows further apart take the
@@ -1038,19 +1048,7 @@ int run_spmm_family(shiro_plan plan, shiro_tuning_t t, const WorkList* wl, SpmmA
   constexpr shiro_dtype out_dt = std::is_same<TOUT, float>::value ? SHIRO_F32 : SHIRO_BF16;
   unsigned nb;
   if (is_walk(t) && a.rid && strides_32(a, in_dt, out_dt)) {
-    // one wavefront per chunk, all chunks in the grid: with a persistent grid
-    // of 16 workgroups per CU and runs of chunks per wavefront the 2^24 R-MAT
-    // panel's backward took 509 us instead of 470, its BF16 forward 194
-    // instead of 172, the ER panel's forward (N = 64) 268 instead of 240
-    const int wv = walk_vec(a.N, in_dt, t.lanes);
-    a.chunks_per_wave = (int32_t)ceil_div(wl->W, (int64_t)kWavesPerBlock << 23);  // below 2^32 threads
-    const int64_t waves = ceil_div(wl->W, (int64_t)a.chunks_per_wave);
-    const dim3 grid((unsigned)(ceil_div(ceil_div(waves, kWavesPerBlock), 8) * 8),
-                    (unsigned)ceil_div(a.N, (int64_t)kWave * wv));
-    a.xcd_remap = t.xcd_remap;
-    if (in_dt == SHIRO_F32) SHIRO_TRY(launch_walk_f32(a, wv, grid, s));
-    else if (out_dt == SHIRO_F32) SHIRO_TRY(launch_walk_bf16_f32(a, wv, grid, s));
-    else SHIRO_TRY(launch_walk_bf16(a, wv, grid, s));
+    SHIRO_TRY(run_walk(t, in_dt, out_dt, a, s));
   } else {
     t.lanes = effective_lanes(t.lanes, a.N, vec);
     // the windowed walk gives each lane group its own chunks
@@ -1644,12 +1642,44 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* val
   return run_spmm_family<bf16_t, bf16_t>(plan, t, wl, a, v, s);
 }
 
+// The walk over the panel's own pattern, dots only: dY row i stays in
+// registers while the wavefront gathers the Bpacked rows of its nonzeros.
+// One tile of a whole panel writes the gradients in place, otherwise the
+// tiles' partial dots are summed (through the value map of a subset plan).
+// 15.5M nonzeros at N = 64 (2^19 R-MAT): 710 us with the wavefront-per-row
+// kernel, which stays for more than four tiles and rows 4 GB apart.
 int launch_sddmm(shiro_plan plan, const shiro_tuning_t& t, const float*, const void* dY,
                  int64_t lddy, const void* Bp, int64_t ldp, int32_t N, shiro_dtype dt,
                  float* dvals, hipStream_t s) {
   if (plan->nnz == 0) return SHIRO_OK;
+  const bool cap = stream_capturing(s);
   const WorkList* wl;
-  SHIRO_TRY(ensure_rows_work(plan, t.chunk, !stream_capturing(s), s, &wl));
+  SHIRO_TRY(ensure_rows_work(plan, t.chunk, !cap, s, &wl));
+  const int tiles = walk_dot_tiles(N, dt, t);
+  SpmmArgs w{};
+  w.ldx = ldp;
+  w.ldd = lddy;
+  if (tiles > 0 && strides_32(w, dt, dt)) {
+    SHIRO_TRY(ensure_row_rid(plan, !cap, s));
+    const bool direct = tiles == 1 && !plan->vmap;
+    if (!direct) SHIRO_TRY(ensure_tdvals(plan, tiles, !cap));
+    w.ptr = plan->row_ptr;
+    w.idx = plan->colmap;
+    w.rid = plan->row_rid;
+    w.D = dY;
+    w.X = Bp;
+    w.x_rows = plan->U;
+    w.dot_out = direct ? dvals + plan->nz_begin : plan->tdvals;
+    w.dot_ld = plan->nnz;
+    w.chunk_row = wl->chunk_row;
+    w.chunk_nz = wl->chunk_nz;
+    w.W = wl->W;
+    w.R = (int32_t)plan->rows;
+    w.N = N;
+    SHIRO_TRY(run_walk(t, dt, dt, w, s));
+    if (direct) return SHIRO_OK;
+    return scatter_values(plan->vmap, plan->tdvals, tiles, plan->nnz, dvals + plan->nz_begin, s);
+  }
   SddmmArgs a{};
   a.ptr = plan->row_ptr;
   a.idx = plan->colmap;
@@ -1664,21 +1694,12 @@ int launch_sddmm(shiro_plan plan, const shiro_tuning_t& t, const float*, const v
   a.W = wl->W;
   a.R = (int32_t)plan->rows;
   a.N = N;
-  a.xcd_remap = t.xcd_remap;
-  shiro_tuning_t tt = t;
-  unsigned nb;
   if (dt == SHIRO_F32) {
-    const int v = vec_for<float>(N, {{dY, lddy}, {Bp, ldp}});
-    tt.lanes = effective_lanes(t.lanes, N, v);
-    SHIRO_TRY(grid_waves(plan, tt, wl->W, kWavesPerBlock, &a.chunks_per_wave, &nb));
-    if (v == 4) return sddmm_dispatch<float, 4>(tt, dim3(nb), s, a);
-    return sddmm_dispatch<float, 1>(tt, dim3(nb), s, a);
+    if (vec_for<float>(N, {{dY, lddy}, {Bp, ldp}}) == 4) return run_sddmm<float, 4>(plan, wl, a, s);
+    return run_sddmm<float, 1>(plan, wl, a, s);
   }
-  const int v = vec_for<bf16_t>(N, {{dY, lddy}, {Bp, ldp}});
-  tt.lanes = effective_lanes(t.lanes, N, v);
-  SHIRO_TRY(grid_waves(plan, tt, wl->W, kWavesPerBlock, &a.chunks_per_wave, &nb));
-  if (v == 8) return sddmm_dispatch<bf16_t, 8>(tt, dim3(nb), s, a);
-  return sddmm_dispatch<bf16_t, 1>(tt, dim3(nb), s, a);
+  if (vec_for<bf16_t>(N, {{dY, lddy}, {Bp, ldp}}) == 8) return run_sddmm<bf16_t, 8>(plan, wl, a, s);
+  return run_sddmm<bf16_t, 1>(plan, wl, a, s);
 }
 
 // Per-block structures (setup): each column block's own CSR over its (row,

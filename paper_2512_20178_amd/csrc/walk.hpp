@@ -117,7 +117,8 @@ __device__ __forceinline__ float wave_sum8(float (&q)[8], int lane) {
 
 // VEC columns per lane; DOT: also the dot of each gathered row with the
 // pattern row's own dense row D (value gradients); SCAT: 0 rows into out,
-// 1 also added to scat, 2 also written to scat.
+// 1 also added to scat, 2 also written to scat, -1 no sums at all (the sampled
+// product: dots only).
 // EDGE: N is no whole number of tiles, so there are idle lanes, and where N is
 // no multiple of VEC the last active lane starts at N - VEC and shares columns
 // with its neighbour (both compute and store the same sums; its shared columns
@@ -135,6 +136,7 @@ __global__ __launch_bounds__(kBlock) void k_walk(SHIRO_SPMM_PARAMS(TIN, TOUT)) {
   typedef typename RI::V VI;
   typedef typename RO::V VO;
   constexpr int UB = kWalkBatch;
+  constexpr bool SUM = SCAT >= 0;
   const int lane = lane_id();
   const int32_t c0 = (int32_t)blockIdx.y * (kWave * VEC) + lane * VEC;
   const bool active = !EDGE || c0 < N;
@@ -204,12 +206,12 @@ __global__ __launch_bounds__(kBlock) void k_walk(SHIRO_SPMM_PARAMS(TIN, TOUT)) {
     float acc[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
-    if (has_head && (int32_t)ptr[i0 + 1] <= j0) to_slot(0, acc);  // row i0 holds nothing here
+    if (SUM && has_head && (int32_t)ptr[i0 + 1] <= j0) to_slot(0, acc);  // row i0 holds nothing here
     auto zero_rows = [&](int32_t lim) {  // complete rows [next, lim) hold no nonzeros
       float z[VEC];
 #pragma unroll
       for (int e = 0; e < VEC; ++e) z[e] = 0.f;
-      for (; next < lim; ++next) put(next, SCAT ? scat_idx[next] : 0, z, true);
+      for (; next < lim; ++next) put(next, SCAT > 0 ? scat_idx[next] : 0, z, true);
     };
     const uint32_t span = i1 > first ? (uint32_t)(i1 - first) : 0u;
     int32_t cur = -1, scur = 0;
@@ -230,9 +232,10 @@ __global__ __launch_bounds__(kBlock) void k_walk(SHIRO_SPMM_PARAMS(TIN, TOUT)) {
         const int32_t kk = lane < j1 - kw ? kw + lane : j1 - 1;
         o.i = WIDE ? idx[kk] : (int32_t)((uint32_t)idx[kk] * xb);
         o.r = rid[kk];
-        o.v = vals[kk];
+        o.v = 0.f;
         o.sc = 0;
-        if constexpr (SCAT != 0) o.sc = scat_idx[o.r];
+        if constexpr (SUM) o.v = vals[kk];
+        if constexpr (SCAT > 0) o.sc = scat_idx[o.r];
         return o;
       };
       Window cw = wload(j0);
@@ -252,11 +255,13 @@ __global__ __launch_bounds__(kBlock) void k_walk(SHIRO_SPMM_PARAMS(TIN, TOUT)) {
           for (int j = 0; j < UB; ++j) x[j] = gather(__builtin_amdgcn_readlane(cw.i, b + j));
           float q[UB];
           auto one = [&](int j) {
-            const float v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cw.v), b + j));
             float xf[VEC];
             RI::unpack(x[j], xf);
+            if constexpr (SUM) {
+              const float v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cw.v), b + j));
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) acc[e] = fmaf(v, xf[e], acc[e]);
+              for (int e = 0; e < VEC; ++e) acc[e] = fmaf(v, xf[e], acc[e]);
+            }
             if constexpr (DOT) {
               float s = 0.f;
 #pragma unroll
@@ -288,14 +293,16 @@ __global__ __launch_bounds__(kBlock) void k_walk(SHIRO_SPMM_PARAMS(TIN, TOUT)) {
               if constexpr (DOT) q[j] = 0.f;
               if (j < n) {
                 if (m >> j & 1) {
-                  flush();
                   const int32_t r = __builtin_amdgcn_readlane(cw.r, b + j);
-                  if (next < r) zero_rows(r);
-                  cur = r;
-                  if constexpr (SCAT != 0) scur = __builtin_amdgcn_readlane(cw.sc, b + j);
-                  next = r + 1;
+                  if constexpr (SUM) {
+                    flush();
+                    if (next < r) zero_rows(r);
+                    next = r + 1;
 #pragma unroll
-                  for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
+                    for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
+                  }
+                  cur = r;
+                  if constexpr (SCAT > 0) scur = __builtin_amdgcn_readlane(cw.sc, b + j);
                   if constexpr (DOT) RI::unpack(dn[j], dcur);
                 }
                 one(j);
@@ -310,9 +317,9 @@ __global__ __launch_bounds__(kBlock) void k_walk(SHIRO_SPMM_PARAMS(TIN, TOUT)) {
         }
         cw = nw;
       }
-      flush();
+      if constexpr (SUM) flush();
     }
-    zero_rows(row_end);
+    if constexpr (SUM) zero_rows(row_end);
   }
 }
 

@@ -34,12 +34,14 @@ int walk_dot(const SpmmArgs& a, dim3 grid, hipStream_t s) {
 
 // The transposed product (dots, overwritten scatter rows) has one type for
 // all its dense operands; only the sums into other rows' types mix them.
+// Dots without carry slots: the sampled product.
 template <typename TIN, typename TOUT, int VEC>
 int walk_form(const SpmmArgs& a, dim3 grid, hipStream_t s) {
   if (a.N < VEC) return set_error(SHIRO_ERR_UNSUPPORTED, "walk: more columns per lane than the matrix has");
   const int scat = a.scat ? a.scat_mode : 0;
   if constexpr (std::is_same<TIN, TOUT>::value) {
     if (a.dot_out) {
+      if (!a.carry) return walk_dot<TIN, TOUT, VEC, -1>(a, grid, s);
       if (scat == 2) return walk_dot<TIN, TOUT, VEC, 2>(a, grid, s);
       if (scat == 1) return walk_dot<TIN, TOUT, VEC, 1>(a, grid, s);
       return walk_dot<TIN, TOUT, VEC, 0>(a, grid, s);
