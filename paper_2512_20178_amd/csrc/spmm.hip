@@ -1583,6 +1583,9 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* val
   a.ldd = dvals && Bp ? ldp : 0;
   a.ldo = dBp ? lddbp : 0;
   a.lds = dB ? lddb : 0;
+  a.X = dY;
+  a.x_rows = plan->rows;
+  a.N = N;
   if (is_walk(t) && !strides_32(a, dt, dt)) t.group_rows = 0;
   if (!plan->tr.built) {
     if (cap) return set_error(SHIRO_ERR_CAPTURING, "backward: transposed pattern not prepared before capture");
@@ -1591,12 +1594,34 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* val
   const WorkList* wl;
   SHIRO_TRY(ensure_cols_work(plan, t.chunk, !cap, s, &wl));
   SHIRO_TRY(ensure_carry(plan, (int64_t)wl->W * 2 * N, !cap));
-  SHIRO_TRY(ensure_tvals(plan, !cap));
-  // values in transposed order: one streaming gather per call, so the hot
-  // loop reads them contiguously instead of through a dependent index
-  // (the dots' buffer is free until the walk and serves as staging area)
-  if (plan->tr.stage_of_csr) SHIRO_TRY(ensure_tdvals(plan, 1, !cap));
-  SHIRO_TRY(values_to_transposed(plan, vals + plan->nz_begin, plan->tvals, plan->tdvals, s));
+  int v;
+  if (dt == SHIRO_F32) v = vec_for<float>(N, {{dY, lddy}, {dBp, lddbp}, {dB, lddb}, {Bp, ldp}});
+  else v = vec_for<bf16_t>(N, {{dY, lddy}, {dBp, lddbp}, {dB, lddb}, {Bp, ldp}});
+  // dvals ride along when one column tile covers N, or (the walk) up to four
+  // tiles, whose partial dots the scatter pass adds
+  const int tiles = is_walk(t) ? walk_dot_tiles(N, dt, t) : 1;
+  const bool fuse = dvals && Bp && (is_walk(t) ? tiles > 0 : (int64_t)effective_lanes(64, N, v) * v >= N);
+  // Small patterns: the walk reads the values (and writes one tile's dots)
+  // through the permutation itself, two launches less (4096-vertex R-MAT,
+  // 2^15 R-MAT of 0.47M nonzeros: 43 -> 37 us), unless the gradients replace
+  // the values it reads.  From about 2M nonzeros on its scattered accesses
+  // cost the row gathers more than the two passes take (2^17 R-MAT 110 -> 114
+  // us, the 2^24 panel 470 -> 524).
+  const int64_t extent = plan->nz_begin + plan->src_nnz;
+  const bool apart = !dvals || dvals >= vals + extent || vals >= dvals + extent;
+  const bool in_walk = is_walk(t) && plan->tr.perm && plan->nnz <= (1 << 20) && (!fuse || (tiles == 1 && apart)) &&
+                       walk_narrow(a, dt == SHIRO_F32 ? 4 : 2, walk_vec(N, dt, t.lanes));
+  if (in_walk) {
+    a.vals = vals + plan->nz_begin;
+    a.vperm = plan->tr.perm;
+  } else {
+    // values in transposed order first, so the hot loop reads them contiguously
+    // (the dots' buffer is free until the walk and serves as staging area)
+    SHIRO_TRY(ensure_tvals(plan, !cap));
+    if (plan->tr.stage_of_csr) SHIRO_TRY(ensure_tdvals(plan, 1, !cap));
+    SHIRO_TRY(values_to_transposed(plan, vals + plan->nz_begin, plan->tvals, plan->tdvals, s));
+    a.vals = plan->tvals;
+  }
   const HotRows* hot = nullptr;
   if (t.group_rows == 3 && t.lds_rows > 0)
     SHIRO_TRY(ensure_hot(plan, SHIRO_KERNEL_SPMM_T, t.lds_rows, !cap, s, &hot));
@@ -1605,9 +1630,6 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* val
   a.hot_src = hot ? hot->hot_src : nullptr;
   a.n_hot = hot ? hot->H : 0;
   a.rid = plan->tr.rid;
-  a.vals = plan->tvals;
-  a.X = dY;
-  a.x_rows = plan->rows;
   a.out = dBp;
   a.scat = dB;
   a.scat_mode = db_overwrite ? 2 : 1;
@@ -1617,24 +1639,16 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* val
   a.carry = plan->carry;
   a.W = wl->W;
   a.R = (int32_t)plan->U;
-  a.N = N;
-  int v;
-  if (dt == SHIRO_F32) v = vec_for<float>(N, {{dY, lddy}, {dBp, lddbp}, {dB, lddb}, {Bp, ldp}});
-  else v = vec_for<bf16_t>(N, {{dY, lddy}, {dBp, lddbp}, {dB, lddb}, {Bp, ldp}});
-  // dvals ride along when one column tile covers N, or (the walk) up to four
-  // tiles, whose partial dots the scatter pass adds
-  const int tiles = is_walk(t) ? walk_dot_tiles(N, dt, t) : 1;
-  const bool fuse = dvals && Bp && (is_walk(t) ? tiles > 0 : (int64_t)effective_lanes(64, N, v) * v >= N);
   if (fuse) {
-    SHIRO_TRY(ensure_tdvals(plan, tiles, !cap));
+    if (!in_walk) SHIRO_TRY(ensure_tdvals(plan, tiles, !cap));
     shiro_tuning_t tt = t;
     if (!is_walk(t)) tt.lanes = 64;  // one tile (effective lanes then cover N)
     a.D = Bp;
-    a.dot_out = plan->tdvals;
+    a.dot_out = in_walk ? dvals + plan->nz_begin : plan->tdvals;
     a.dot_ld = plan->nnz;
     if (dt == SHIRO_F32) SHIRO_TRY((run_spmm_family<float, float>(plan, tt, wl, a, v, s)));
     else SHIRO_TRY((run_spmm_family<bf16_t, bf16_t>(plan, tt, wl, a, v, s)));
-    SHIRO_TRY(values_from_transposed(plan, plan->tdvals, tiles, dvals + plan->nz_begin, plan->tvals, s));
+    if (!in_walk) SHIRO_TRY(values_from_transposed(plan, plan->tdvals, tiles, dvals + plan->nz_begin, plan->tvals, s));
     if (dvals_done) *dvals_done = true;
     return SHIRO_OK;
   }

@@ -12,7 +12,8 @@ namespace shiro {
 struct SpmmArgs {
   const int64_t* ptr;       // R + 1
   const int32_t* idx;       // nnz: row of X to gather
-  const float* vals;        // values in pattern order
+  const float* vals;        // values in pattern order, or (the walk) through vperm
+  const int32_t* vperm;     // optional (the walk): where vals and dot_out hold nonzero k
   const void* D;            // optional: dense row per pattern row, dotted with each gathered row
   int64_t ldd;
   float* dot_out;           // nnz: the dots, in pattern order (when D is set)
@@ -39,7 +40,8 @@ struct SpmmArgs {
 
 #define SHIRO_SPMM_PARAMS(TIN, TOUT)                                                          \
   const int64_t *__restrict__ ptr, const int32_t *__restrict__ idx,                           \
-      const float *__restrict__ vals, const TIN *__restrict__ D, int64_t ldd,                 \
+      const float *__restrict__ vals, const int32_t *__restrict__ vperm,                      \
+      const TIN *__restrict__ D, int64_t ldd,                                                 \
       float *__restrict__ dot_out, int64_t dot_ld,                                            \
       const TIN *__restrict__ X, int64_t ldx, TOUT *__restrict__ out, int64_t ldo,           \
       TOUT *__restrict__ scat, int64_t lds, const int32_t *__restrict__ scat_idx,             \
@@ -49,14 +51,14 @@ struct SpmmArgs {
       const int32_t *__restrict__ hot_src, int32_t n_hot
 
 #define SHIRO_SPMM_ARGS(TIN, TOUT, a)                                                          \
-  (a).ptr, (a).idx, (a).vals, reinterpret_cast<const TIN*>((a).D), (a).ldd, (a).dot_out, (a).dot_ld, \
+  (a).ptr, (a).idx, (a).vals, (a).vperm, reinterpret_cast<const TIN*>((a).D), (a).ldd, (a).dot_out, (a).dot_ld, \
       reinterpret_cast<const TIN*>((a).X), (a).ldx,                                            \
       reinterpret_cast<TOUT*>((a).out), (a).ldo, reinterpret_cast<TOUT*>((a).scat), (a).lds,   \
       (a).scat_idx, (a).chunk_row, (a).chunk_nz, (a).rid, (a).carry, (a).W, (a).R, (a).N,     \
       (a).chunks_per_wave, (a).xcd_remap, (a).scat_mode, (a).hot_src, (a).n_hot
 
 #define SHIRO_SPMM_NAMES                                                                       \
-  ptr, idx, vals, D, ldd, dot_out, dot_ld, X, ldx, out, ldo, scat, lds, scat_idx, chunk_row, chunk_nz, rid, \
+  ptr, idx, vals, vperm, D, ldd, dot_out, dot_ld, X, ldx, out, ldo, scat, lds, scat_idx, chunk_row, chunk_nz, rid, \
       carry, W, R, N, cpw, xcd_remap, scat_mode, hot_src, n_hot
 
 // Logical workgroup index: with xcd_remap, workgroups that the dispatcher
@@ -66,6 +68,14 @@ __device__ __forceinline__ int32_t logical_block(int32_t remap) {
   const int32_t b = blockIdx.x, g = gridDim.x;
   if (!remap || (g & 7)) return b;
   return (b & 7) * (g >> 3) + (b >> 3);
+}
+
+// The walk gathers by 32-bit row offsets of whole dwords: elements of `size`
+// bytes, vec of them per lane.
+inline bool walk_narrow(const SpmmArgs& a, int64_t size, int vec) {
+  const int64_t xb = a.ldx * size;
+  return a.x_rows * xb < ((int64_t)1 << 32) && (uintptr_t)a.X % 4 == 0 && xb % 4 == 0 && a.N * size % 4 == 0 &&
+         vec * size >= 4;
 }
 
 // The nonzero walk (walk_*.hip).  The grid covers a.W chunks, a.chunks_per_wave

@@ -126,9 +126,12 @@ __device__ __forceinline__ float wave_sum8(float (&q)[8], int lane) {
 // WIDE: the gathered matrix spans 4 GB or more, or its rows are not whole
 // dwords; otherwise a gather is a buffer load of a 32-bit row offset, which
 // saves five of the instructions that bound the walk of cached rows.
+// PERM: nonzero k's value is vals[vperm[k]] and its dot goes to
+// dot_out[vperm[k]] (an instance of its own: carried as a runtime case it cost
+// the other patterns 4%, 2^18 R-MAT training step 360 -> 375 us).
 // A launch with several column tiles leaves one set of dots per tile, dot_ld
 // apart.
-template <typename TIN, typename TOUT, int VEC, bool DOT, int SCAT, bool EDGE, bool WIDE>
+template <typename TIN, typename TOUT, int VEC, bool DOT, int SCAT, bool EDGE, bool WIDE, bool PERM>
 __global__ __launch_bounds__(kBlock) void k_walk(SHIRO_SPMM_PARAMS(TIN, TOUT)) {
   typedef RowVec<TIN, VEC> RI;
   typedef RowVec<TOUT, VEC> RO;
@@ -224,25 +227,33 @@ __global__ __launch_bounds__(kBlock) void k_walk(SHIRO_SPMM_PARAMS(TIN, TOUT)) {
       // window of 64 nonzeros from kw: lane l holds nonzero kw + l (past the
       // chunk's end, its last nonzero again)
       struct Window {
-        int32_t i, r, sc;
+        int32_t i, r, sc, p;
         float v;
       };
-      auto wload = [&](int32_t kw) {
+      auto place = [&](int32_t kw) { return lane < j1 - kw ? kw + lane : j1 - 1; };
+      // where vals holds the window's values: loaded a window before the rest
+      auto pload = [&](int32_t kw) { return PERM ? vperm[place(kw)] : 0; };
+      auto wload = [&](int32_t kw, int32_t p) {
         Window o;
-        const int32_t kk = lane < j1 - kw ? kw + lane : j1 - 1;
+        const int32_t kk = place(kw);
         o.i = WIDE ? idx[kk] : (int32_t)((uint32_t)idx[kk] * xb);
         o.r = rid[kk];
+        o.p = p;
         o.v = 0.f;
         o.sc = 0;
-        if constexpr (SUM) o.v = vals[kk];
+        if constexpr (SUM) o.v = vals[PERM ? p : kk];
         if constexpr (SCAT > 0) o.sc = scat_idx[o.r];
         return o;
       };
-      Window cw = wload(j0);
+      Window cw = wload(j0, pload(j0));
+      int32_t np = PERM && j1 - j0 > kWave ? pload(j0 + kWave) : 0;
       for (int32_t left = j1 - j0; left > 0; left -= kWave) {
         const int32_t kw = j1 - left;
         Window nw = cw;
-        if (left > kWave) nw = wload(kw + kWave);
+        if (left > kWave) {
+          nw = wload(kw + kWave, np);
+          if (PERM && left > 2 * kWave) np = pload(kw + 2 * kWave);
+        }
         // bit l: nonzero kw + l opens another row than the one before it
         const int32_t prev = __builtin_amdgcn_update_dpp(cur, cw.r, 0x138, 0xF, 0xF, false);  // wave_shr:1
         uint64_t opens = __ballot(cw.r != prev);
@@ -312,7 +323,10 @@ __global__ __launch_bounds__(kBlock) void k_walk(SHIRO_SPMM_PARAMS(TIN, TOUT)) {
           if constexpr (DOT) {
             const float s = wave_sum8(q, lane);
             const int j = lane >> 3;
-            if ((lane & 7) == 0 && j < n) dot_out[(int64_t)blockIdx.y * dot_ld + kw + b + j] = s;
+            // lane 8 j holds the dot of nonzero b + j, lane b + j its place
+            int32_t at_j = kw + b + j;
+            if constexpr (PERM) at_j = __builtin_amdgcn_ds_bpermute((b + j) << 2, cw.p);
+            if ((lane & 7) == 0 && j < n) dot_out[(int64_t)blockIdx.y * dot_ld + at_j] = s;
           }
         }
         cw = nw;

@@ -8,18 +8,21 @@ namespace shiro {
 
 template <typename TIN, typename TOUT, int VEC, bool DOT, int SCAT, bool EDGE>
 int walk_go(const SpmmArgs& a, dim3 grid, hipStream_t s) {
-  // 32-bit row offsets of whole dwords
-  const int64_t xb = a.ldx * (int64_t)sizeof(TIN);
-  const bool narrow = a.x_rows * xb < ((int64_t)1 << 32) && (uintptr_t)a.X % 4 == 0 && xb % 4 == 0 &&
-                      a.N * (int64_t)sizeof(TIN) % 4 == 0 && VEC * (int)sizeof(TIN) >= 4;
   if constexpr (VEC * (int)sizeof(TIN) >= 4) {
-    if (narrow) {
-      k_walk<TIN, TOUT, VEC, DOT, SCAT, EDGE, false><<<grid, kBlock, 0, s>>>(SHIRO_SPMM_ARGS(TIN, TOUT, a));
+    if (walk_narrow(a, sizeof(TIN), VEC)) {
+      if constexpr (EDGE && SCAT >= 0 && std::is_same<TIN, TOUT>::value) {
+        if (a.vperm) {
+          k_walk<TIN, TOUT, VEC, DOT, SCAT, EDGE, false, true><<<grid, kBlock, 0, s>>>(SHIRO_SPMM_ARGS(TIN, TOUT, a));
+          SHIRO_LAUNCH_CHECK();
+          return SHIRO_OK;
+        }
+      }
+      k_walk<TIN, TOUT, VEC, DOT, SCAT, EDGE, false, false><<<grid, kBlock, 0, s>>>(SHIRO_SPMM_ARGS(TIN, TOUT, a));
       SHIRO_LAUNCH_CHECK();
       return SHIRO_OK;
     }
   }
-  k_walk<TIN, TOUT, VEC, DOT, SCAT, EDGE, true><<<grid, kBlock, 0, s>>>(SHIRO_SPMM_ARGS(TIN, TOUT, a));
+  k_walk<TIN, TOUT, VEC, DOT, SCAT, EDGE, true, false><<<grid, kBlock, 0, s>>>(SHIRO_SPMM_ARGS(TIN, TOUT, a));
   SHIRO_LAUNCH_CHECK();
   return SHIRO_OK;
 }
@@ -28,7 +31,7 @@ int walk_go(const SpmmArgs& a, dim3 grid, hipStream_t s) {
 // without dots idle lanes cost one exec mask per stored row.
 template <typename TIN, typename TOUT, int VEC, int SCAT>
 int walk_dot(const SpmmArgs& a, dim3 grid, hipStream_t s) {
-  if (a.N % (kWave * VEC) == 0) return walk_go<TIN, TOUT, VEC, true, SCAT, false>(a, grid, s);
+  if (a.N % (kWave * VEC) == 0 && !a.vperm) return walk_go<TIN, TOUT, VEC, true, SCAT, false>(a, grid, s);
   return walk_go<TIN, TOUT, VEC, true, SCAT, true>(a, grid, s);
 }
 
@@ -37,6 +40,8 @@ int walk_dot(const SpmmArgs& a, dim3 grid, hipStream_t s) {
 // Dots without carry slots: the sampled product.
 template <typename TIN, typename TOUT, int VEC>
 int walk_form(const SpmmArgs& a, dim3 grid, hipStream_t s) {
+  if (a.vperm && !walk_narrow(a, sizeof(TIN), VEC))
+    return set_error(SHIRO_ERR_UNSUPPORTED, "walk: values through a permutation need 32-bit row offsets");
   if (a.N < VEC) return set_error(SHIRO_ERR_UNSUPPORTED, "walk: more columns per lane than the matrix has");
   const int scat = a.scat ? a.scat_mode : 0;
   if constexpr (std::is_same<TIN, TOUT>::value) {
