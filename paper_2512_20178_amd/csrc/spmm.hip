@@ -48,39 +48,57 @@ __global__ void k_merge_path(const int64_t* __restrict__ ptr, int32_t R, int64_t
   chunk_nz[w] = (int32_t)(d - lo);
 }
 
-// flag[w] = 1 if chunk w starts a row that a later chunk finishes.
-__global__ void k_split_flags(const int64_t* __restrict__ ptr, int32_t R,
-                              const int32_t* __restrict__ chunk_row,
-                              const int32_t* __restrict__ chunk_nz, int32_t W,
-                              int32_t* __restrict__ flag) {
+// last[w] = the last chunk holding the row that chunk w starts and a later
+// chunk finishes, or -1.
+__global__ void k_split_last(const int64_t* __restrict__ ptr, int32_t R,
+                             const int32_t* __restrict__ chunk_row,
+                             const int32_t* __restrict__ chunk_nz, int32_t W,
+                             int32_t* __restrict__ last) {
   const int64_t w = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (w >= W) return;
   const int32_t r = chunk_row[w + 1];
-  int32_t f = 0;
+  int32_t l = -1;
   if (r < R) {
     const int64_t rs = ptr[r];
-    f = (chunk_nz[w + 1] > rs) && (rs >= chunk_nz[w]);
+    if (chunk_nz[w + 1] > rs && rs >= chunk_nz[w]) {
+      // last chunk we with chunk_row[we] <= r, i.e. the first with chunk_row[we + 1] > r
+      int64_t lo = w + 1, hi = W - 1;
+      while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (chunk_row[mid + 1] > r) hi = mid; else lo = mid + 1;
+      }
+      l = (int32_t)lo;
+    }
   }
-  flag[w] = f;
+  last[w] = l;
 }
 
-// split[3 pos[w] ..] = (w, last chunk holding row r, r) for flagged chunks.
-__global__ void k_split_emit(const int32_t* __restrict__ flag, const int64_t* __restrict__ pos,
+// Splits of at most kFixupSmall pieces count in the low 32 bits, the others
+// in the high ones, so one scan places both lists.
+struct SplitCount {
+  const int32_t* last;
+  __device__ int64_t operator()(int64_t w) const {
+    if (last[w] < 0) return 0;
+    return last[w] - w + 1 <= kFixupSmall ? 1 : (int64_t)1 << 32;
+  }
+};
+struct SplitPlace {
+  int64_t* pos;
+  __device__ void operator()(int64_t w, int64_t prefix, int64_t) const { pos[w] = prefix; }
+};
+
+// split[3 s ..] = (w, last chunk holding row r, r), the small splits first,
+// chunks ascending in each list; pos[W] holds both counts.
+__global__ void k_split_emit(const int32_t* __restrict__ last, const int64_t* __restrict__ pos,
                              const int32_t* __restrict__ chunk_row, int32_t W,
                              int32_t* __restrict__ split) {
   const int64_t w = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (w >= W || !flag[w]) return;
-  const int32_t r = chunk_row[w + 1];
-  // last chunk we with chunk_row[we] <= r, i.e. the first with chunk_row[we + 1] > r
-  int64_t lo = w + 1, hi = W - 1;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (chunk_row[mid + 1] > r) hi = mid; else lo = mid + 1;
-  }
-  const int64_t s = pos[w];
+  if (w >= W || last[w] < 0) return;
+  const bool small = last[w] - w + 1 <= kFixupSmall;
+  const int64_t s = small ? (pos[w] & 0xffffffff) : (pos[W] & 0xffffffff) + (pos[w] >> 32);
   split[3 * s] = (int32_t)w;
-  split[3 * s + 1] = (int32_t)lo;
-  split[3 * s + 2] = r;
+  split[3 * s + 1] = last[w];
+  split[3 * s + 2] = chunk_row[w + 1];
 }
 
 // ---------------------------------------------------------------------------
@@ -789,11 +807,11 @@ __global__ void k_iota(uint32_t* p, int64_t n) {
 // packed column (every packed column has at least one entry).
 __global__ void k_transpose_finish(const uint32_t* __restrict__ skeys,
                                    const uint32_t* __restrict__ perm, int64_t nnz,
-                                   const int64_t* __restrict__ row_ptr, int64_t rows, int64_t U,
+                                   const int32_t* __restrict__ rid, int64_t U,
                                    int32_t* __restrict__ trow, int64_t* __restrict__ tptr) {
   for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz;
        j += (int64_t)gridDim.x * blockDim.x) {
-    trow[j] = (int32_t)row_of(row_ptr, rows, perm[j]);
+    trow[j] = rid[perm[j]];
     if (j == 0 || skeys[j] != skeys[j - 1]) tptr[skeys[j]] = j;
     if (j == nnz - 1) tptr[U] = nnz;
   }
@@ -1111,70 +1129,44 @@ int build_worklist(const int64_t* ptr, int64_t R, int64_t nnz, int32_t chunk, Wo
       ptr, (int32_t)R, nnz, chunk, wl->W, wl->chunk_row, wl->chunk_nz);
   SHIRO_LAUNCH_CHECK();
   wl->nsplit = 0;
-  if (wl->W == 0) return SHIRO_OK;
-  // list of rows cut by chunk boundaries (temporary buffers, freed here)
-  int32_t* flag = nullptr;
-  int64_t* pos = nullptr;
-  void* tmp = nullptr;
-  int64_t* h_n = nullptr;
-  auto cleanup = [&] {
-    dev_free(flag);
-    dev_free(pos);
-    dev_free(tmp);
-    if (h_n) (void)hipHostFree(h_n);
-  };
-  int rc;
-  if ((rc = dev_alloc_n(&flag, wl->W)) || (rc = dev_alloc_n(&pos, (int64_t)wl->W + 1)) ||
-      (rc = dev_alloc(&tmp, scan_scratch_bytes(wl->W)))) {
-    cleanup();
-    return rc;
-  }
-  if (hipHostMalloc((void**)&h_n, 8, hipHostMallocDefault) != hipSuccess) {
-    cleanup();
-    return set_error(SHIRO_ERR_OOM, "work list: pinned allocation failed");
-  }
-  k_split_flags<<<grid_for(wl->W, 1 << 20), kBlock, 0, s>>>(ptr, (int32_t)R, wl->chunk_row,
-                                                            wl->chunk_nz, wl->W, flag);
-  if ((rc = exclusive_scan_i32_to_i64(flag, wl->W, pos, pos + wl->W, tmp, s)) ||
-      hipMemcpyAsync(h_n, pos + wl->W, 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess) {
-    cleanup();
-    return rc ? rc : set_error(SHIRO_ERR_HIP, "work list: split count failed");
-  }
-  wl->nsplit = (int32_t)*h_n;
-  if (wl->nsplit > 0) {
-    if ((rc = dev_alloc_n(&wl->split, 3 * (int64_t)wl->nsplit))) {
-      cleanup();
-      return rc;
-    }
-    k_split_emit<<<grid_for(wl->W, 1 << 20), kBlock, 0, s>>>(flag, pos, wl->chunk_row, wl->W, wl->split);
-  }
-  hipError_t e = hipStreamSynchronize(s);
-  cleanup();
-  if (e != hipSuccess) return set_error(SHIRO_ERR_HIP, "work list: split list failed");
   wl->nsmall = 0;
-  if (wl->nsplit == 0) return SHIRO_OK;
-  // order the list: splits of at most kFixupSmall pieces first (setup only)
-  std::vector<int32_t> h((size_t)wl->nsplit * 3), o;
-  o.reserve(h.size());
-  if (hipMemcpy(h.data(), wl->split, h.size() * 4, hipMemcpyDeviceToHost) != hipSuccess)
-    return set_error(SHIRO_ERR_HIP, "work list: reading the split list failed");
-  for (int pass = 0; pass < 2; ++pass)
-    for (size_t i = 0; i < (size_t)wl->nsplit; ++i) {
-      const bool small = h[3 * i + 1] - h[3 * i] + 1 <= kFixupSmall;
-      if (small == (pass == 0)) o.insert(o.end(), h.begin() + 3 * i, h.begin() + 3 * i + 3);
-    }
-  for (size_t i = 0; i < (size_t)wl->nsplit; ++i)
-    if (h[3 * i + 1] - h[3 * i] + 1 <= kFixupSmall) ++wl->nsmall;
-  if (hipMemcpy(wl->split, o.data(), o.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
-    return set_error(SHIRO_ERR_HIP, "work list: writing the split list failed");
-  return SHIRO_OK;
+  if (wl->W == 0) return SHIRO_OK;
+  // list of rows cut by chunk boundaries (one temporary block, freed here)
+  const int64_t W = wl->W;
+  const int64_t last_bytes = (W * 4 + 255) / 256 * 256, pos_bytes = ((W + 1) * 8 + 255) / 256 * 256;
+  char* tmp = nullptr;
+  SHIRO_TRY(dev_alloc(reinterpret_cast<void**>(&tmp), last_bytes + pos_bytes + scan_scratch_bytes(W)));
+  int32_t* last = reinterpret_cast<int32_t*>(tmp);
+  int64_t* pos = reinterpret_cast<int64_t*>(tmp + last_bytes);
+  auto list = [&]() -> int {
+    k_split_last<<<grid_for(W, 1 << 20), kBlock, 0, s>>>(ptr, (int32_t)R, wl->chunk_row, wl->chunk_nz, wl->W, last);
+    SHIRO_LAUNCH_CHECK();
+    SHIRO_TRY(scan_generic(SplitCount{last}, W, SplitPlace{pos}, pos + W, tmp + last_bytes + pos_bytes, s));
+    int64_t n = 0;
+    SHIRO_HIP(hipMemcpyAsync(&n, pos + W, 8, hipMemcpyDeviceToHost, s));
+    SHIRO_HIP(hipStreamSynchronize(s));
+    const int32_t nsmall = (int32_t)(n & 0xffffffff), nsplit = nsmall + (int32_t)(n >> 32);
+    if (nsplit == 0) return SHIRO_OK;
+    SHIRO_TRY(dev_alloc_n(&wl->split, 3 * (int64_t)nsplit));
+    k_split_emit<<<grid_for(W, 1 << 20), kBlock, 0, s>>>(last, pos, wl->chunk_row, wl->W, wl->split);
+    SHIRO_LAUNCH_CHECK();
+    SHIRO_HIP(hipStreamSynchronize(s));
+    wl->nsplit = nsplit;
+    wl->nsmall = nsmall;
+    return SHIRO_OK;
+  };
+  const int rc = list();
+  dev_free(tmp);
+  return rc;
 }
 
 int build_transposed(shiro_plan plan, hipStream_t s) {
   Transposed& tr = plan->tr;
   if (tr.built) return SHIRO_OK;
   const int64_t nnz = plan->nnz, U = plan->U;
+  // the rows of the entries come from the row ids (a binary search per entry
+  // took 131 us for 4.2M nonzeros, the gather 40)
+  SHIRO_TRY(ensure_row_rid(plan, true, s));
   SHIRO_TRY(dev_alloc_n(&tr.ptr, U + 1));
   SHIRO_TRY(dev_alloc_n(&tr.row, nnz > 0 ? nnz : 1));
   SHIRO_TRY(dev_alloc_n(&tr.perm, nnz > 0 ? nnz : 1));
@@ -1200,8 +1192,7 @@ int build_transposed(shiro_plan plan, hipStream_t s) {
   SHIRO_TRY(radix_sort_pairs(reinterpret_cast<const uint32_t*>(plan->colmap), iota, skeys,
                              reinterpret_cast<uint32_t*>(tr.perm), nnz, bits, sort_tmp, s));
   k_transpose_finish<<<grid_for(nnz), kBlock, 0, s>>>(skeys, reinterpret_cast<uint32_t*>(tr.perm),
-                                                       nnz, plan->row_ptr, plan->rows, U, tr.row,
-                                                       tr.ptr);
+                                                       nnz, plan->row_rid, U, tr.row, tr.ptr);
   SHIRO_LAUNCH_CHECK();
   // subset plans read the caller's values through the value map
   if (plan->vmap) SHIRO_TRY(launch_compose(tr.perm, plan->vmap, nnz, s));
