@@ -49,12 +49,14 @@ __all__ = [
 ]
 
 _DT = {torch.float32: _lib.F32, torch.bfloat16: _lib.BF16}
+_DTYPES = tuple(_DT)
+_MODES = {"batched": _lib.MODE_BATCHED, "per_block": _lib.MODE_PER_BLOCK}
 _KERNELS = {"spmm": _lib.KERNEL_SPMM, "spmm_t": _lib.KERNEL_SPMM_T, "sddmm": _lib.KERNEL_SDDMM,
             "partial_c": _lib.KERNEL_PARTIAL_C, "aggregate_c": _lib.KERNEL_AGGREGATE_C}
 
 
 def _L():
-    return _lib.load()
+    return _lib._lib or _lib.load()
 
 
 # ---------------------------------------------------------------------------
@@ -87,9 +89,17 @@ def use_torch_allocator(enable: bool = True) -> None:
     _alloc_hooks = hooks
 
 
+# torch's own accessor of the current stream's handle, without the Stream
+# object that torch.cuda.current_stream() builds (0.1 against 2.8 us)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _dt(t: torch.dtype) -> int:
@@ -99,17 +109,19 @@ def _dt(t: torch.dtype) -> int:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _ld(t: torch.Tensor) -> int:
-    if t.dim() != 2:
+    shape = t.shape
+    if len(shape) != 2:
         raise ValueError("dense operands must be 2-D")
-    if t.numel() == 0:  # an empty operand has no meaningful strides
-        return max(t.shape[1], 1)
-    if t.stride(1) != 1 or t.stride(0) < t.shape[1]:
+    if shape[0] == 0 or shape[1] == 0:  # an empty operand has no meaningful strides
+        return max(shape[1], 1)
+    s0, s1 = t.stride()
+    if s1 != 1 or s0 < shape[1]:
         raise ValueError("dense operands must be row-major with unit column stride")
-    return t.stride(0)
+    return s0
 
 
 def _dev(t: torch.Tensor):
@@ -120,17 +132,18 @@ def _dev(t: torch.Tensor):
 def _mat(t: Optional[torch.Tensor], name: str, min_rows: int, N: int, dtypes=None):
     """Check a dense operand before its pointer reaches the library: on the
     GPU, 2-D, at least min_rows rows of exactly N columns, row-major with unit
-    column stride, of an allowed dtype."""
+    column stride, of an allowed dtype.  Returns its leading dimension."""
     if t is None:
-        return
+        return 0
     _dev(t)
-    if t.dim() != 2:
+    shape = t.shape
+    if len(shape) != 2:
         raise ValueError(f"{name} must be 2-D")
-    if t.shape[0] < min_rows or t.shape[1] != N:
-        raise ValueError(f"{name} must have at least {min_rows} rows and {N} columns, got {tuple(t.shape)}")
+    if shape[0] < min_rows or shape[1] != N:
+        raise ValueError(f"{name} must have at least {min_rows} rows and {N} columns, got {tuple(shape)}")
     if dtypes is not None and t.dtype not in dtypes:
         raise TypeError(f"{name} must be one of {dtypes}, got {t.dtype}")
-    _ld(t)
+    return _ld(t)
 
 
 def _vec(t: Optional[torch.Tensor], name: str, min_numel: int):
@@ -151,6 +164,18 @@ def version() -> int:
     return int(_L().shiro_version())
 
 
+def _dims(plan) -> Tuple[int, int, int]:
+    """(rows, n_cols, U) of a plan, kept in it once the selection has run: the
+    panel's pattern, and with it all three, never changes after that."""
+    d = getattr(plan, "_sizes", None)
+    if d is None:
+        inf = plan.info()
+        d = (inf["rows"], inf["n_cols"], inf["U"])
+        if d[2] >= 0 and isinstance(plan, Plan):
+            plan._sizes = d
+    return d
+
+
 class Plan:
     """Library-owned plan of rank p's panel (freed when garbage collected)."""
 
@@ -158,9 +183,12 @@ class Plan:
         self._h = ctypes.c_void_p(handle)
         self.device = device
         self._graphs = []
+        self._sizes = None
         inf = self.info()
         # entries of the CSR's value array the plan reads (vals, dvals)
         self.value_extent = value_extent if value_extent is not None else inf["nz_begin"] + inf["nnz"]
+        # every one of those entries is a nonzero of the plan
+        self._whole = inf["nnz"] == self.value_extent
         self.R = None  # sum of |Rows(A^(p,q))| once select_c_rows ran
 
     @property
@@ -181,6 +209,7 @@ class Plan:
         if getattr(self, "_h", None) is not None and self._h.value:
             _L().shiro_plan_destroy(self._h)
             self._h = ctypes.c_void_p(0)
+            self._sizes = None
 
     def __del__(self):
         try:
@@ -205,7 +234,7 @@ class Plan:
             holder.append(gid.value)
 
     def replay(self, graph_id: int, stream=None):
-        _lib.check(_L().shiro_graph_launch(self._h, int(graph_id), ctypes.c_void_p(_stream(stream))))
+        _lib.check(_L().shiro_graph_launch(self._h, int(graph_id), _stream(stream)))
 
 
 def partition(row_ptr: torch.Tensor, col: torch.Tensor, n_rows: int, n_cols: int, P: int, p: int,
@@ -288,43 +317,39 @@ def block_nnz(plan: Plan, stream=None) -> torch.Tensor:
 
 def pack_B(plan: Plan, B: torch.Tensor, out: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """Bpacked[u] = B[unique_cols[u]] (bit-exact), shape U x N."""
-    inf = plan.info()
-    U = inf["U"]
+    _, n_cols, U = _dims(plan)
     if U < 0:
         raise ShiroError(-6, "pack_B: call select_rows first")
     _dev(B)
     if B.dim() != 2:
         raise ValueError("B must be 2-D")
     N = B.shape[1]
-    _mat(B, "B", inf["n_cols"], N, tuple(_DT))
+    ldb = _mat(B, "B", n_cols, N, _DTYPES)
     if out is None:
-        out = torch.empty(U, N, dtype=B.dtype, device=B.device)
-    _mat(out, "out", U, N, (B.dtype,))
-    _lib.check(_L().shiro_pack_B(plan.handle, _ptr(B), _ld(B), N, _dt(B.dtype), _ptr(out), _ld(out),
-                                 ctypes.c_void_p(_stream(stream))))
+        out = B.new_empty((U, N))
+    ldo = _mat(out, "out", U, N, (B.dtype,))
+    _lib.check(_L().shiro_pack_B(plan.handle, B.data_ptr(), ldb, N, _DT[B.dtype], out.data_ptr(), ldo,
+                                 _stream(stream)))
     return out
 
 
 def spmm(plan: Plan, vals: torch.Tensor, Bpacked: torch.Tensor, out: Optional[torch.Tensor] = None,
          out_dtype: Optional[torch.dtype] = None, mode: str = "batched", stream=None) -> torch.Tensor:
     """Y = A^(p,:) Bpacked (rows x N); vals is the CSR's float32 value array."""
-    inf = plan.info()
-    rows = inf["rows"]
+    rows, _, U = _dims(plan)
     _dev(Bpacked)
     if Bpacked.dim() != 2:
         raise ValueError("Bpacked must be 2-D")
     N = Bpacked.shape[1]
-    _mat(Bpacked, "Bpacked", max(inf["U"], 0), N, tuple(_DT))
+    ldp = _mat(Bpacked, "Bpacked", max(U, 0), N, _DTYPES)
     _vec(vals, "vals", plan.value_extent)
-    out_dtype = out_dtype or Bpacked.dtype
     if out is None:
-        out = torch.empty(rows, N, dtype=out_dtype, device=Bpacked.device)
-    _mat(out, "out", rows, N, tuple(_DT))
-    if mode not in ("batched", "per_block"):
+        out = Bpacked.new_empty((rows, N), dtype=out_dtype or Bpacked.dtype)
+    ldo = _mat(out, "out", rows, N, _DTYPES)
+    if mode not in _MODES:
         raise ValueError("mode must be 'batched' or 'per_block'")
-    m = {"batched": _lib.MODE_BATCHED, "per_block": _lib.MODE_PER_BLOCK}[mode]
-    _lib.check(_L().shiro_spmm(plan.handle, _ptr(vals), _ptr(Bpacked), _ld(Bpacked), N, _dt(Bpacked.dtype),
-                               _ptr(out), _ld(out), _dt(out.dtype), m, ctypes.c_void_p(_stream(stream))))
+    _lib.check(_L().shiro_spmm(plan.handle, _ptr(vals), Bpacked.data_ptr(), ldp, N, _DT[Bpacked.dtype],
+                               out.data_ptr(), ldo, _DT[out.dtype], _MODES[mode], _stream(stream)))
     return out
 
 
@@ -355,27 +380,26 @@ def spmm_backward(plan: Plan, vals: torch.Tensor, dY: torch.Tensor, Bpacked: Opt
     Pass the output tensors to compute; None skips an output.  With
     dB_overwrite the rows dB[unique_cols] are overwritten instead of added to
     (the other rows are left as they are)."""
-    inf = plan.info()
+    rows, n_cols, U = _dims(plan)
     _dev(dY)
     if dY.dim() != 2:
         raise ValueError("dY must be 2-D")
     N = dY.shape[1]
     dt = _dt(dY.dtype)
-    U = max(inf["U"], 0)
-    _mat(dY, "dY", inf["rows"], N)
-    _mat(Bpacked, "Bpacked", U, N, (dY.dtype,))
-    _mat(dBpacked, "dBpacked", U, N, (dY.dtype,))
-    _mat(dB, "dB", inf["n_cols"], N, (dY.dtype,))
+    U = max(U, 0)
+    same = (dY.dtype,)
+    ldy = _mat(dY, "dY", rows, N)
+    ldp = _mat(Bpacked, "Bpacked", U, N, same)
+    lddbp = _mat(dBpacked, "dBpacked", U, N, same)
+    lddb = _mat(dB, "dB", n_cols, N, same)
     if dBpacked is not None or dB is not None:
         _vec(vals, "vals", plan.value_extent)
     _vec(dvals, "dvals", plan.value_extent)
     if dvals is not None and Bpacked is None:
         raise ValueError("dvals needs Bpacked")
     _lib.check(_L().shiro_spmm_backward(
-        plan.handle, _ptr(vals), _ptr(dY), _ld(dY), _ptr(Bpacked), _ld(Bpacked) if Bpacked is not None else N,
-        N, dt, _ptr(dBpacked), _ld(dBpacked) if dBpacked is not None else N, _ptr(dB),
-        _ld(dB) if dB is not None else N, _ptr(dvals), _lib.DB_OVERWRITE if dB_overwrite else 0,
-        ctypes.c_void_p(_stream(stream))))
+        plan.handle, _ptr(vals), dY.data_ptr(), ldy, _ptr(Bpacked), ldp or N, N, dt, _ptr(dBpacked), lddbp or N,
+        _ptr(dB), lddb or N, _ptr(dvals), _lib.DB_OVERWRITE if dB_overwrite else 0, _stream(stream)))
     return dBpacked, dB, dvals
 
 
@@ -611,11 +635,16 @@ class ShiroSpMM(torch.autograd.Function):
         plan = ctx.plan
         dY = dY.to(ctx.B_dtype).contiguous()
         dvals = dB = None
+        # zeros only where the backward leaves entries unwritten: values outside
+        # the panel (or its subset), rows of B no column of the panel selects
         if ctx.needs_input_grad[0]:
-            dvals = torch.zeros_like(vals)
+            whole = plan._whole and vals.numel() == plan.value_extent
+            dvals = torch.empty_like(vals) if whole else torch.zeros_like(vals)
         if ctx.needs_input_grad[1]:
-            dB = torch.zeros(ctx.B_shape, dtype=ctx.B_dtype, device=dY.device)
-        # dB is zero-filled here, so its selected rows are simply written
+            shape = ctx.B_shape
+            fill = torch.empty if _dims(plan)[2] == shape[0] and shape[1] > 0 else torch.zeros
+            dB = fill(shape, dtype=ctx.B_dtype, device=dY.device)
+        # no row of dB holds anything yet, so its selected rows are simply written
         spmm_backward(plan, vals, dY, Bp, None, dB, dvals, dB_overwrite=True)
         return dvals, dB, None, None
 

@@ -124,3 +124,31 @@ def test_staged_value_permutation(shiro, n_rows):
     want.index_add_(0, col.reshape(-1), (vals * G[rows, 0]).double())
     assert torch.equal(dB[:, 0].double(), want)
     assert torch.equal(dvals, G[rows, 0] * B[col.reshape(-1), 0])
+
+
+@pytest.mark.parametrize("P,p", [(1, 0), (4, 1)])
+def test_autograd_gradients_complete(shiro, P, p):
+    """Gradients that the backward writes whole are not zero-filled first; the
+    others are: stale memory never shows, a panel's gradients are zero outside
+    it."""
+    A = synth.small_rmat(9, 40, P=P, p=p)
+    dev = torch.device("cuda")
+    Ad, Ac = A.to(dev), oracle.Csr.from_synth(A)
+    plan = shiro.partition(Ad.row_ptr, Ad.col, A.n_rows, A.n_cols, P, p)
+    shiro.select_rows(plan)
+    N = 16
+    B = synth.dense(A.n_cols, N, 0, synth.STREAM_B).to(dev)
+    G = synth.dense(plan.info()["rows"], N, 0, synth.STREAM_DY).to(dev)
+    for t in (A.nnz, A.n_cols * N):  # what the allocator hands out next holds NaN
+        stale = [torch.full((t,), float("nan"), device=dev) for _ in range(4)]
+        del stale
+    vals, Bl = Ad.vals.clone().requires_grad_(True), B.clone().requires_grad_(True)
+    Y = shiro.shiro_spmm(plan, vals, Bl)
+    dvals, dB = torch.autograd.grad(Y, (vals, Bl), G)
+    Bn, Gn = B.cpu().numpy(), G.cpu().numpy()
+    assert oracle.rel_err(dB.cpu().numpy(), oracle.spmm_t(Ac, Gn, None), oracle.spmm_t(Ac, Gn, None, abs_mode=True)) <= 1e-5
+    nz = slice(Ac.nz_begin, Ac.nz_begin + Ac.nnz_panel)
+    dv = dvals.cpu().numpy()
+    assert oracle.rel_err(dv[nz], oracle.sddmm(Ac, Gn, Bn, None), oracle.sddmm(Ac, Gn, Bn, None, abs_mode=True)) <= 1e-5
+    rest = np.delete(dv, np.arange(A.nnz)[nz])
+    assert not rest.any()
