@@ -231,6 +231,13 @@ int values_to_transposed(shiro_plan plan, const float* vals, float* tvals, float
 // vals[perm[j]] = sum over the sets t < sets of tvals[j + t nnz].
 int values_from_transposed(shiro_plan plan, const float* tvals, int sets, float* vals, float* stage, hipStream_t s);
 
+// ---- dots.hip ---------------------------------------------------------------
+// out[map ? map[k] : k] = D[rid[k], 0:N] . X[idx[k], 0:N] for widths that
+// dots_narrow names.
+bool dots_narrow(int32_t N);
+int launch_dots(const int32_t* idx, const int32_t* rid, const void* D, int64_t ldd, const void* X, int64_t ldx,
+                const int32_t* map, float* out, int64_t nnz, int32_t N, shiro_dtype dt, hipStream_t s);
+
 // ---- spmm.hip ---------------------------------------------------------------
 int build_worklist(const int64_t* ptr, int64_t R, int64_t nnz, int32_t chunk, WorkList* wl,
                    hipStream_t s);

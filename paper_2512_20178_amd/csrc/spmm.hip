@@ -1647,17 +1647,23 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* val
   return run_spmm_family<bf16_t, bf16_t>(plan, t, wl, a, v, s);
 }
 
-// The walk over the panel's own pattern, dots only: dY row i stays in
+// Up to 64 columns: dots.hip.  Wider: the walk over the panel's own pattern,
+// dots only: dY row i stays in
 // registers while the wavefront gathers the Bpacked rows of its nonzeros.
 // One tile of a whole panel writes the gradients in place, otherwise the
 // tiles' partial dots are summed (through the value map of a subset plan).
-// 15.5M nonzeros at N = 64 (2^19 R-MAT): 710 us with the wavefront-per-row
-// kernel, which stays for more than four tiles and rows 4 GB apart.
+// The wavefront-per-row kernel (710 against 342 us for 15.5M nonzeros of a
+// 2^19 R-MAT at N = 64) stays for more than four tiles and rows 4 GB apart.
 int launch_sddmm(shiro_plan plan, const shiro_tuning_t& t, const float*, const void* dY,
                  int64_t lddy, const void* Bp, int64_t ldp, int32_t N, shiro_dtype dt,
                  float* dvals, hipStream_t s) {
   if (plan->nnz == 0) return SHIRO_OK;
   const bool cap = stream_capturing(s);
+  if (dots_narrow(N)) {
+    SHIRO_TRY(ensure_row_rid(plan, !cap, s));
+    return launch_dots(plan->colmap, plan->row_rid, dY, lddy, Bp, ldp, plan->vmap, dvals + plan->nz_begin, plan->nnz,
+                       N, dt, s);
+  }
   const WorkList* wl;
   SHIRO_TRY(ensure_rows_work(plan, t.chunk, !cap, s, &wl));
   const int tiles = walk_dot_tiles(N, dt, t);

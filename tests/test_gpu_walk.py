@@ -152,3 +152,26 @@ def test_autograd_gradients_complete(shiro, P, p):
     assert oracle.rel_err(dv[nz], oracle.sddmm(Ac, Gn, Bn, None), oracle.sddmm(Ac, Gn, Bn, None, abs_mode=True)) <= 1e-5
     rest = np.delete(dv, np.arange(A.nnz)[nz])
     assert not rest.any()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("N", [3, 4, 5, 31, 32, 33, 47, 63, 64, 65, 130])
+def test_value_gradients_alone(shiro, N, dtype):
+    """dvals without dB at the width edges of its kernels (lane groups of 8 and
+    16 from 4 to 64 columns, the walk outside), padded rows, and a nonzero
+    count that is no whole number of windows."""
+    A = _case(100 + N)
+    dev = torch.device("cuda")
+    Ad, Ac = A.to(dev), oracle.Csr.from_synth(A)
+    plan = shiro.partition(Ad.row_ptr, Ad.col, A.n_rows, A.n_cols, 1, 0)
+    U, _ = shiro.select_rows(plan)
+    B = synth.dense(A.n_cols, N, N, synth.STREAM_B).to(dtype)
+    G = synth.dense(A.n_rows, N, N, synth.STREAM_DY).to(dtype)
+    Bn, Gn = B.float().numpy(), G.float().numpy()
+    ref, den = oracle.sddmm(Ac, Gn, Bn, None), oracle.sddmm(Ac, Gn, Bn, None, abs_mode=True)
+    for pad in (0, 1):
+        Bp = shiro.pack_B(plan, B.to(dev), out=torch.empty(U, N + pad, dtype=dtype, device=dev)[:, :N])
+        Gd = torch.zeros(A.n_rows, N + pad, dtype=dtype, device=dev)[:, :N].copy_(G)
+        dvals = torch.full((A.nnz,), float("nan"), device=dev)
+        shiro.spmm_backward(plan, None, Gd, Bp, dvals=dvals)
+        assert oracle.rel_err(dvals.cpu().numpy(), ref, den) <= 1e-5, pad
