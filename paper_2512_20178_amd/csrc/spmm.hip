@@ -1119,8 +1119,8 @@ int run_spmm_family(shiro_plan plan, shiro_tuning_t t, const WorkList* wl, SpmmA
 // ===========================================================================
 // host entry points
 // ===========================================================================
-int build_worklist(const int64_t* ptr, int64_t R, int64_t nnz, int32_t chunk, WorkList* wl,
-                   hipStream_t s) {
+static int fill_worklist(const int64_t* ptr, int64_t R, int64_t nnz, int32_t chunk, WorkList* wl, char** tmp,
+                         hipStream_t s) {
   wl->chunk = chunk;
   wl->W = (int32_t)ceil_div(R + nnz, chunk);
   SHIRO_TRY(dev_alloc_n(&wl->chunk_row, (int64_t)wl->W + 1));
@@ -1131,38 +1131,45 @@ int build_worklist(const int64_t* ptr, int64_t R, int64_t nnz, int32_t chunk, Wo
   wl->nsplit = 0;
   wl->nsmall = 0;
   if (wl->W == 0) return SHIRO_OK;
-  // list of rows cut by chunk boundaries (one temporary block, freed here)
+  // list of rows cut by chunk boundaries (in one temporary block)
   const int64_t W = wl->W;
   const int64_t last_bytes = (W * 4 + 255) / 256 * 256, pos_bytes = ((W + 1) * 8 + 255) / 256 * 256;
+  SHIRO_TRY(dev_alloc(reinterpret_cast<void**>(tmp), last_bytes + pos_bytes + scan_scratch_bytes(W)));
+  int32_t* last = reinterpret_cast<int32_t*>(*tmp);
+  int64_t* pos = reinterpret_cast<int64_t*>(*tmp + last_bytes);
+  k_split_last<<<grid_for(W, 1 << 20), kBlock, 0, s>>>(ptr, (int32_t)R, wl->chunk_row, wl->chunk_nz, wl->W, last);
+  SHIRO_LAUNCH_CHECK();
+  SHIRO_TRY(scan_generic(SplitCount{last}, W, SplitPlace{pos}, pos + W, *tmp + last_bytes + pos_bytes, s));
+  int64_t n = 0;
+  SHIRO_HIP(hipMemcpyAsync(&n, pos + W, 8, hipMemcpyDeviceToHost, s));
+  SHIRO_HIP(hipStreamSynchronize(s));
+  const int32_t nsmall = (int32_t)(n & 0xffffffff), nsplit = nsmall + (int32_t)(n >> 32);
+  if (nsplit == 0) return SHIRO_OK;
+  SHIRO_TRY(dev_alloc_n(&wl->split, 3 * (int64_t)nsplit));
+  k_split_emit<<<grid_for(W, 1 << 20), kBlock, 0, s>>>(last, pos, wl->chunk_row, wl->W, wl->split);
+  SHIRO_LAUNCH_CHECK();
+  SHIRO_HIP(hipStreamSynchronize(s));
+  wl->nsplit = nsplit;
+  wl->nsmall = nsmall;
+  return SHIRO_OK;
+}
+
+int build_worklist(const int64_t* ptr, int64_t R, int64_t nnz, int32_t chunk, WorkList* wl,
+                   hipStream_t s) {
   char* tmp = nullptr;
-  SHIRO_TRY(dev_alloc(reinterpret_cast<void**>(&tmp), last_bytes + pos_bytes + scan_scratch_bytes(W)));
-  int32_t* last = reinterpret_cast<int32_t*>(tmp);
-  int64_t* pos = reinterpret_cast<int64_t*>(tmp + last_bytes);
-  auto list = [&]() -> int {
-    k_split_last<<<grid_for(W, 1 << 20), kBlock, 0, s>>>(ptr, (int32_t)R, wl->chunk_row, wl->chunk_nz, wl->W, last);
-    SHIRO_LAUNCH_CHECK();
-    SHIRO_TRY(scan_generic(SplitCount{last}, W, SplitPlace{pos}, pos + W, tmp + last_bytes + pos_bytes, s));
-    int64_t n = 0;
-    SHIRO_HIP(hipMemcpyAsync(&n, pos + W, 8, hipMemcpyDeviceToHost, s));
-    SHIRO_HIP(hipStreamSynchronize(s));
-    const int32_t nsmall = (int32_t)(n & 0xffffffff), nsplit = nsmall + (int32_t)(n >> 32);
-    if (nsplit == 0) return SHIRO_OK;
-    SHIRO_TRY(dev_alloc_n(&wl->split, 3 * (int64_t)nsplit));
-    k_split_emit<<<grid_for(W, 1 << 20), kBlock, 0, s>>>(last, pos, wl->chunk_row, wl->W, wl->split);
-    SHIRO_LAUNCH_CHECK();
-    SHIRO_HIP(hipStreamSynchronize(s));
-    wl->nsplit = nsplit;
-    wl->nsmall = nsmall;
-    return SHIRO_OK;
-  };
-  const int rc = list();
+  const int rc = fill_worklist(ptr, R, nnz, chunk, wl, &tmp, s);
   dev_free(tmp);
+  if (rc != SHIRO_OK) {  // nothing is kept unless every step succeeds
+    dev_free(wl->chunk_row);
+    dev_free(wl->chunk_nz);
+    dev_free(wl->split);
+    *wl = WorkList{};
+  }
   return rc;
 }
 
-int build_transposed(shiro_plan plan, hipStream_t s) {
+static int fill_transposed(shiro_plan plan, hipStream_t s) {
   Transposed& tr = plan->tr;
-  if (tr.built) return SHIRO_OK;
   const int64_t nnz = plan->nnz, U = plan->U;
   // the rows of the entries come from the row ids (a binary search per entry
   // took 131 us for 4.2M nonzeros, the gather 40)
@@ -1175,7 +1182,6 @@ int build_transposed(shiro_plan plan, hipStream_t s) {
     scan_generic(
         [] __device__(int64_t) -> int64_t { return 0; }, 0,
         [] __device__(int64_t, int64_t, int64_t) {}, tr.ptr, nullptr, s);
-    tr.built = true;
     return SHIRO_OK;
   }
   // scratch: iota values + sort scratch; the sorted keys are the entries' rows
@@ -1197,10 +1203,24 @@ int build_transposed(shiro_plan plan, hipStream_t s) {
   // subset plans read the caller's values through the value map
   if (plan->vmap) SHIRO_TRY(launch_compose(tr.perm, plan->vmap, nnz, s));
   SHIRO_HIP(hipStreamSynchronize(s));
-  SHIRO_TRY(build_value_permutation(plan, s));
+  return build_value_permutation(plan, s);
+}
+
+int build_transposed(shiro_plan plan, hipStream_t s) {
+  Transposed& tr = plan->tr;
+  if (tr.built) return SHIRO_OK;
+  const int rc = fill_transposed(plan, s);
+  if (rc != SHIRO_OK) {  // nothing is kept unless every step succeeds
+    for (void* p : {(void*)tr.ptr, (void*)tr.row, (void*)tr.perm, (void*)tr.rid, (void*)tr.stage_of_csr,
+                    (void*)tr.entry_of_stage})
+      dev_free(p);
+    tr = Transposed{};
+    return rc;
+  }
   tr.built = true;
   return SHIRO_OK;
 }
+
 
 int build_segments(shiro_plan plan, hipStream_t s) {
   BlockSegments& sg = plan->seg;

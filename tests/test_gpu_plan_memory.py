@@ -1,0 +1,133 @@
+"""Device memory of a plan: what preparing it allocates, what happens when an
+allocation fails part way, and that no buffer a captured graph may hold is
+given back while the plan lives.  A counting allocator (torch tensors) stands
+behind the library in every test."""
+import contextlib
+
+import pytest
+import torch
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def shiro():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2512_20178_amd as s
+
+    s._lib.load()
+    return s
+
+
+_HOOKS = []
+
+
+class Arena:
+    """refuse(bytes) true: no memory for that request."""
+
+    def __init__(self):
+        self.live, self.freed, self.asked = {}, [], []
+        self.refuse = lambda n: False
+
+    def held(self):
+        return sum(t.numel() for t in self.live.values())
+
+    def alloc(self, n, ctx):
+        self.asked.append(int(n))
+        if self.refuse(int(n)):
+            return None
+        t = torch.empty(int(n), dtype=torch.uint8, device="cuda")
+        self.live[t.data_ptr()] = t
+        return t.data_ptr()
+
+    def free(self, p, n, ctx):
+        self.freed.append(p)
+        self.live.pop(p)
+
+
+@contextlib.contextmanager
+def arena(shiro):
+    a = Arena()
+    hooks = (shiro._lib.ALLOC_FN(a.alloc), shiro._lib.FREE_FN(a.free))
+    _HOOKS.append(hooks)  # outlive any plan a failing test leaves behind
+    assert shiro._L().shiro_set_allocator(hooks[0], hooks[1], None) == 0
+    try:
+        yield a
+    finally:
+        shiro.use_torch_allocator(False)
+
+
+def _backward(shiro, plan, vals, N, dtype=torch.float32):
+    dev = vals.device
+    inf = plan.info()
+    Bp = synth.dense(inf["U"], N, 1, synth.STREAM_B).to(dev).to(dtype)
+    G = synth.dense(inf["rows"], N, 2, synth.STREAM_DY).to(dev).to(dtype)
+    dBp = torch.full((inf["U"], N), float("nan"), dtype=dtype, device=dev)
+    dvals = torch.full_like(vals, float("nan"))
+    shiro.spmm_backward(plan, vals, G, Bp, dBpacked=dBp, dvals=dvals)
+    return dBp, dvals
+
+
+def test_failed_allocation_leaves_nothing_behind(shiro):
+    """Each allocation of prepare fails once: the call reports OOM, a second
+    call succeeds with the same results, and the plan gives back every block
+    when it is destroyed."""
+    A, N = synth.small_rmat(10, 16), 32
+    Ad = A.to(torch.device("cuda"))
+    plan = shiro.partition(Ad.row_ptr, Ad.col, A.n_rows, A.n_cols, 1, 0)
+    shiro.select_rows(plan)
+    want = _backward(shiro, plan, Ad.vals, N)
+    failures = 0
+    with arena(shiro) as a:
+        for k in range(100):
+            plan = shiro.partition(Ad.row_ptr, Ad.col, A.n_rows, A.n_cols, 1, 0)
+            shiro.select_rows(plan)
+            last = len(a.asked) + k + 1
+            a.refuse = lambda n: len(a.asked) == last
+            try:
+                shiro.prepare(plan, N)
+                done = len(a.asked) < last
+            except shiro.ShiroError as e:
+                assert e.name == "OOM"
+                done, failures = False, failures + 1
+            a.refuse = lambda n: False
+            shiro.prepare(plan, N)
+            got = _backward(shiro, plan, Ad.vals, N)
+            plan.close()
+            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), k
+            assert not a.live, f"allocation {k}: {len(a.live)} blocks not given back"
+            if done:
+                break
+    assert done and failures >= 8
+
+
+def _large(n_rows=1 << 19, deg=25):
+    """13.1M nonzeros, deg ascending columns a row; small whole numbers, so
+    every gradient at N = 1 is exact."""
+    dev = torch.device("cuda")
+    g = torch.Generator(device=dev)
+    g.manual_seed(7)
+    step = n_rows // deg
+    col = torch.randint(step, (n_rows, deg), generator=g, device=dev) + torch.arange(deg, device=dev) * step
+    row_ptr = torch.arange(0, n_rows * deg + 1, deg, device=dev)
+    vals = torch.randint(-3, 4, (n_rows * deg,), generator=g, device=dev).float()
+    G = torch.randint(-2, 3, (n_rows, 1), generator=g, device=dev).float()
+    B = torch.randint(-2, 3, (n_rows, 1), generator=g, device=dev).float()
+    return row_ptr, col, vals, G, B
+
+
+def _check_large(shiro, plan, case):
+    row_ptr, col, vals, G, B = case
+    n_rows, deg = col.shape
+    Bp = shiro.pack_B(plan, B)
+    dB = torch.zeros_like(B)
+    dvals = torch.full_like(vals, float("nan"))
+    shiro.spmm_backward(plan, vals, G, Bp, dB=dB, dvals=dvals, dB_overwrite=True)
+    rows = torch.arange(n_rows, device=vals.device).repeat_interleave(deg)
+    want = torch.zeros(n_rows, dtype=torch.float64, device=vals.device)
+    want.index_add_(0, col.reshape(-1), (vals * G[rows, 0]).double())
+    assert torch.equal(dB[:, 0].double(), want)
+    assert torch.equal(dvals, G[rows, 0] * B[col.reshape(-1), 0])
