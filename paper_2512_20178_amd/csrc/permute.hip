@@ -127,12 +127,6 @@ __global__ __launch_bounds__(kBlock) void k_invert(const int32_t* __restrict__ p
     inv[perm[j]] = (uint32_t)j;
 }
 
-__global__ __launch_bounds__(kBlock) void k_window_keys(const uint32_t* __restrict__ inv, int64_t n,
-                                                        uint32_t* __restrict__ key) {
-  for (int64_t k = blockIdx.x * (int64_t)kBlock + threadIdx.x; k < n; k += (int64_t)gridDim.x * kBlock)
-    key[k] = inv[k] >> kWinShift;
-}
-
 __global__ __launch_bounds__(kBlock) void k_places(const int32_t* __restrict__ entry, const int32_t* __restrict__ perm,
                                                    int64_t n, int32_t* __restrict__ place) {
   for (int64_t q = blockIdx.x * (int64_t)kBlock + threadIdx.x; q < n; q += (int64_t)gridDim.x * kBlock)
@@ -148,31 +142,28 @@ unsigned window_blocks(int64_t n) {
 }  // namespace
 
 // After plan->tr.perm: the staged order of large whole-panel patterns (subset
-// plans read the caller's array through a map that skips positions).
+// plans read the caller's array through a map that skips positions).  One
+// array more than the direct permutation needs: the inverse permutation and,
+// after the sort, the places live in the scratch that the transposed pattern's
+// own sort has just used, and the places end in perm's memory.
 int build_value_permutation(shiro_plan plan, hipStream_t s) {
   Transposed& tr = plan->tr;
   const int64_t n = plan->nnz;
   if (n < kStagedMin || plan->vmap) return SHIRO_OK;
-  auto al = [](int64_t b) { return (b + 255) / 256 * 256; };
-  SHIRO_TRY(ensure_scratch(plan, 3 * al(n * 4) + sort_scratch_bytes(n)));
-  char* p = reinterpret_cast<char*>(plan->scratch);
-  uint32_t* inv = reinterpret_cast<uint32_t*>(p);
-  uint32_t* key = reinterpret_cast<uint32_t*>(p + al(n * 4));
-  uint32_t* skey = reinterpret_cast<uint32_t*>(p + 2 * al(n * 4));
-  void* tmp = p + 3 * al(n * 4);
-  SHIRO_TRY(dev_alloc_n(&tr.stage_of_csr, n));
+  SHIRO_TRY(ensure_scratch(plan, sort_scratch_bytes(n)));
   SHIRO_TRY(dev_alloc_n(&tr.entry_of_stage, n));
+  uint32_t* inv = reinterpret_cast<uint32_t*>(plan->scratch);  // the sort's first n words, which it only reads
   k_invert<<<grid_for(n), kBlock, 0, s>>>(tr.perm, n, inv);
-  SHIRO_LAUNCH_CHECK();
-  k_window_keys<<<grid_for(n), kBlock, 0, s>>>(inv, n, key);
   SHIRO_LAUNCH_CHECK();
   int bits = 0;
   while (((int64_t)1 << bits) < ceil_div(n, (int64_t)1 << kWinShift)) ++bits;
-  SHIRO_TRY(radix_sort_pairs(key, inv, skey, reinterpret_cast<uint32_t*>(tr.entry_of_stage), n, bits, tmp, s));
-  k_places<<<grid_for(n), kBlock, 0, s>>>(tr.entry_of_stage, tr.perm, n, tr.stage_of_csr);
+  SHIRO_TRY(radix_sort_keys(inv, reinterpret_cast<uint32_t*>(tr.entry_of_stage), n, kWinShift, bits, plan->scratch, s));
+  int32_t* place = reinterpret_cast<int32_t*>(inv);
+  k_places<<<grid_for(n), kBlock, 0, s>>>(tr.entry_of_stage, tr.perm, n, place);
   SHIRO_LAUNCH_CHECK();
+  SHIRO_HIP(hipMemcpyAsync(tr.perm, place, (size_t)n * 4, hipMemcpyDeviceToDevice, s));
   SHIRO_HIP(hipStreamSynchronize(s));
-  dev_free(tr.perm);
+  tr.stage_of_csr = tr.perm;
   tr.perm = nullptr;
   return SHIRO_OK;
 }

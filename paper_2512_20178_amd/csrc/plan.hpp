@@ -219,6 +219,11 @@ int64_t sort_scratch_bytes(int64_t n);
 int radix_sort_pairs(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* keys_out,
                      uint32_t* vals_out, int64_t n, int key_bits, void* scratch, hipStream_t s);
 
+// The keys in stable order of their key_bits bits from `shift` on.  keys_in
+// may be the first n words of scratch (only read); same scratch.
+int radix_sort_keys(const uint32_t* keys_in, uint32_t* keys_out, int64_t n, int shift, int key_bits, void* scratch,
+                    hipStream_t s);
+
 // ---- permute.hip ------------------------------------------------------------
 // out[k] = vals[map[k]].
 int gather_values(const int32_t* map, const float* vals, int64_t n, float* out, hipStream_t s);

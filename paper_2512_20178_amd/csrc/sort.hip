@@ -1,5 +1,5 @@
-// Stable LSD radix sort of (uint32 key, uint32 value) pairs, 8 bits per pass,
-// without atomics.
+// Stable LSD radix sort of (uint32 key, uint32 value) pairs, or of keys alone,
+// 8 bits per pass, without atomics.
 //
 // A workgroup owns a tile of 4096 consecutive keys, split into 64 sub-tiles
 // of 64 keys (one key per lane).  Inside a sub-tile, eight ballots give every
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(kBlock) void k_sort_scatter(
       const uint32_t d = (key[j] >> shift) & (kRadix - 1);
       const int64_t pos = base[d] + cnt[st][d] + rank[j];
       keys_out[pos] = key[j];
-      vals_out[pos] = vals[idx];
+      if (vals) vals_out[pos] = vals[idx];
     }
   }
 }
@@ -135,28 +135,52 @@ int64_t sort_scratch_bytes(int64_t n) {
          + scan_scratch_bytes(nh);
 }
 
+namespace {
+
+struct SortScratch {
+  uint32_t *tk, *tv;  // n each
+  int32_t* hist;
+  int64_t* hoff;
+  void* scan_tmp;
+  int64_t ntiles;
+  SortScratch(void* scratch, int64_t n) : ntiles(ceil_div(n, kSortTile)) {
+    const int64_t nh = ntiles * kRadix;
+    char* p = reinterpret_cast<char*>(scratch);
+    auto take = [&](int64_t bytes) {
+      char* r = p;
+      p += (bytes + 255) / 256 * 256;
+      return r;
+    };
+    tk = reinterpret_cast<uint32_t*>(take(n * 4));
+    tv = reinterpret_cast<uint32_t*>(take(n * 4));
+    hist = reinterpret_cast<int32_t*>(take(nh * 4));
+    hoff = reinterpret_cast<int64_t*>(take(nh * 8));
+    scan_tmp = take(scan_scratch_bytes(nh));
+  }
+};
+
+int sort_pass(const uint32_t* keys, const uint32_t* vals, int64_t n, int shift, uint32_t* keys_out,
+              uint32_t* vals_out, const SortScratch& t, hipStream_t s) {
+  k_sort_count<<<(unsigned)t.ntiles, kBlock, 0, s>>>(keys, n, shift, t.hist, t.ntiles);
+  SHIRO_LAUNCH_CHECK();
+  SHIRO_TRY(exclusive_scan_i32_to_i64(t.hist, t.ntiles * kRadix, t.hoff, nullptr, t.scan_tmp, s));
+  k_sort_scatter<<<(unsigned)t.ntiles, kBlock, 0, s>>>(keys, vals, n, shift, t.hoff, t.ntiles, keys_out, vals_out);
+  SHIRO_LAUNCH_CHECK();
+  return SHIRO_OK;
+}
+
+unsigned copy_grid(int64_t n) { return (unsigned)ceil_div(n, kBlock) < 65536u ? (unsigned)ceil_div(n, kBlock) : 65536u; }
+
+}  // namespace
+
 int radix_sort_pairs(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* keys_out,
                      uint32_t* vals_out, int64_t n, int key_bits, void* scratch, hipStream_t s) {
   if (n <= 0) return SHIRO_OK;
-  const int64_t ntiles = ceil_div(n, kSortTile);
-  const int64_t nh = ntiles * kRadix;
-  char* p = reinterpret_cast<char*>(scratch);
-  auto take = [&](int64_t bytes) {
-    char* r = p;
-    p += (bytes + 255) / 256 * 256;
-    return r;
-  };
-  uint32_t* tk = reinterpret_cast<uint32_t*>(take(n * 4));
-  uint32_t* tv = reinterpret_cast<uint32_t*>(take(n * 4));
-  int32_t* hist = reinterpret_cast<int32_t*>(take(nh * 4));
-  int64_t* hoff = reinterpret_cast<int64_t*>(take(nh * 8));
-  void* scan_tmp = take(scan_scratch_bytes(nh));
-
-  int passes = (key_bits + kRadixBits - 1) / kRadixBits;
-  const unsigned g = (unsigned)ceil_div(n, kBlock) < 65536u ? (unsigned)ceil_div(n, kBlock) : 65536u;
+  const SortScratch t(scratch, n);
+  const int passes = (key_bits + kRadixBits - 1) / kRadixBits;
   if (passes == 0) {
-    k_copy_u32<<<g, kBlock, 0, s>>>(keys_in, keys_out, n);
-    k_copy_u32<<<g, kBlock, 0, s>>>(vals_in, vals_out, n);
+    k_copy_u32<<<copy_grid(n), kBlock, 0, s>>>(keys_in, keys_out, n);
+    k_copy_u32<<<copy_grid(n), kBlock, 0, s>>>(vals_in, vals_out, n);
     SHIRO_LAUNCH_CHECK();
     return SHIRO_OK;
   }
@@ -164,19 +188,31 @@ int radix_sort_pairs(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t*
   const uint32_t* ck = keys_in;
   const uint32_t* cv = vals_in;
   for (int pass = 0; pass < passes; ++pass) {
-    const bool last = pass == passes - 1;
     const bool to_out = ((passes - 1 - pass) % 2) == 0;
-    uint32_t* ok = to_out ? keys_out : tk;
-    uint32_t* ov = to_out ? vals_out : tv;
-    (void)last;
-    const int shift = pass * kRadixBits;
-    k_sort_count<<<(unsigned)ntiles, kBlock, 0, s>>>(ck, n, shift, hist, ntiles);
-    SHIRO_LAUNCH_CHECK();
-    SHIRO_TRY(exclusive_scan_i32_to_i64(hist, nh, hoff, nullptr, scan_tmp, s));
-    k_sort_scatter<<<(unsigned)ntiles, kBlock, 0, s>>>(ck, cv, n, shift, hoff, ntiles, ok, ov);
-    SHIRO_LAUNCH_CHECK();
+    uint32_t* ok = to_out ? keys_out : t.tk;
+    uint32_t* ov = to_out ? vals_out : t.tv;
+    SHIRO_TRY(sort_pass(ck, cv, n, pass * kRadixBits, ok, ov, t, s));
     ck = ok;
     cv = ov;
+  }
+  return SHIRO_OK;
+}
+
+int radix_sort_keys(const uint32_t* keys_in, uint32_t* keys_out, int64_t n, int shift, int key_bits, void* scratch,
+                    hipStream_t s) {
+  if (n <= 0) return SHIRO_OK;
+  const SortScratch t(scratch, n);
+  const int passes = (key_bits + kRadixBits - 1) / kRadixBits;
+  if (passes == 0) {
+    k_copy_u32<<<copy_grid(n), kBlock, 0, s>>>(keys_in, keys_out, n);
+    SHIRO_LAUNCH_CHECK();
+    return SHIRO_OK;
+  }
+  const uint32_t* ck = keys_in;
+  for (int pass = 0; pass < passes; ++pass) {
+    uint32_t* ok = ((passes - 1 - pass) % 2) == 0 ? keys_out : t.tv;
+    SHIRO_TRY(sort_pass(ck, nullptr, n, shift + pass * kRadixBits, ok, nullptr, t, s));
+    ck = ok;
   }
   return SHIRO_OK;
 }

@@ -131,3 +131,25 @@ def _check_large(shiro, plan, case):
     want.index_add_(0, col.reshape(-1), (vals * G[rows, 0]).double())
     assert torch.equal(dB[:, 0].double(), want)
     assert torch.equal(dvals, G[rows, 0] * B[col.reshape(-1), 0])
+
+
+def test_large_pattern_setup_memory(shiro):
+    """Preparing a pattern in the staged order allocates one array (4 bytes a
+    nonzero) more than the direct permutation needs, gives no large block back
+    and allocates none twice."""
+    case = _large()
+    row_ptr, col, vals, _, _ = case
+    n, nnz = col.shape[0], vals.numel()
+    with arena(shiro) as a:
+        plan = shiro.partition(row_ptr, col.reshape(-1).int(), n, n, 1, 0)
+        shiro.select_rows(plan)
+        first = len(a.asked)
+        before = dict(a.live)
+        shiro.prepare(plan, 1)
+        big = [b for b in a.asked[first:] if b >= 2 * nnz]
+        assert sum(a.asked[first:]) <= 28 * nnz + 8 * n + (16 << 20)
+        assert len(big) == 7
+        assert all(p in a.live for p in before)
+        _check_large(shiro, plan, case)
+        plan.close()
+        assert not a.live
