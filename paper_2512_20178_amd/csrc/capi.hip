@@ -1011,10 +1011,10 @@ SHIRO_API int shiro_prepare(shiro_plan plan, int32_t N, shiro_dtype dt, uint32_t
     if (t.group_rows == 3 && t.lds_rows > 0) SHIRO_TRY(ensure_hot(plan, SHIRO_KERNEL_SPMM, t.lds_rows, true, s, &hot));
   }
   if (ops & SHIRO_OP_BACKWARD) {
-    SHIRO_TRY(build_transposed(plan, s));
-    SHIRO_TRY(ensure_tvals(plan, true));
     const shiro_tuning_t t = tuning_for(plan, SHIRO_KERNEL_SPMM_T, N, dt);
+    SHIRO_TRY(ensure_tvals(plan, true));
     SHIRO_TRY(ensure_tdvals(plan, is_walk(t) ? std::max(walk_dot_tiles(N, dt, t), 1) : 1, true));
+    SHIRO_TRY(build_transposed(plan, s));
     SHIRO_TRY(ensure_cols_work(plan, t.chunk, true, s, &wl));
     SHIRO_TRY(ensure_carry(plan, (int64_t)wl->W * 2 * N, true));
     const HotRows* hot;

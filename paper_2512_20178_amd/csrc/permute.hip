@@ -141,6 +141,8 @@ unsigned window_blocks(int64_t n) {
 
 }  // namespace
 
+bool staged_values(shiro_plan plan) { return plan->nnz >= kStagedMin && !plan->vmap; }
+
 // After plan->tr.perm: the staged order of large whole-panel patterns (subset
 // plans read the caller's array through a map that skips positions).  One
 // array more than the direct permutation needs: the inverse permutation and,
@@ -149,9 +151,12 @@ unsigned window_blocks(int64_t n) {
 int build_value_permutation(shiro_plan plan, hipStream_t s) {
   Transposed& tr = plan->tr;
   const int64_t n = plan->nnz;
-  if (n < kStagedMin || plan->vmap) return SHIRO_OK;
+  if (!staged_values(plan)) return SHIRO_OK;
   SHIRO_TRY(ensure_scratch(plan, sort_scratch_bytes(n)));
-  SHIRO_TRY(dev_alloc_n(&tr.entry_of_stage, n));
+  // without memory for it the direct permutation stays
+  const int rc = dev_alloc_n(&tr.entry_of_stage, n);
+  if (rc == SHIRO_ERR_OOM) return SHIRO_OK;
+  SHIRO_TRY(rc);
   uint32_t* inv = reinterpret_cast<uint32_t*>(plan->scratch);  // the sort's first n words, which it only reads
   k_invert<<<grid_for(n), kBlock, 0, s>>>(tr.perm, n, inv);
   SHIRO_LAUNCH_CHECK();

@@ -229,7 +229,9 @@ int radix_sort_keys(const uint32_t* keys_in, uint32_t* keys_out, int64_t n, int 
 int gather_values(const int32_t* map, const float* vals, int64_t n, float* out, hipStream_t s);
 // out[map ? map[k] : k] = sum over the sets t < sets of in[k + t n].
 int scatter_values(const int32_t* map, const float* in, int sets, int64_t n, float* out, hipStream_t s);
-// Values between CSR order and transposed order (plan->tr).
+// Values between CSR order and transposed order (plan->tr).  Patterns that
+// staged_values names take the staged order when there is memory for it.
+bool staged_values(shiro_plan plan);
 int build_value_permutation(shiro_plan plan, hipStream_t s);
 // tvals[j] = vals[perm[j]]; stage: nnz floats of scratch.
 int values_to_transposed(shiro_plan plan, const float* vals, float* tvals, float* stage, hipStream_t s);

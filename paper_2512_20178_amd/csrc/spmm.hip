@@ -1209,6 +1209,10 @@ static int fill_transposed(shiro_plan plan, hipStream_t s) {
 int build_transposed(shiro_plan plan, hipStream_t s) {
   Transposed& tr = plan->tr;
   if (tr.built) return SHIRO_OK;
+  if (staged_values(plan)) {  // what the backward cannot do without, before what it can
+    SHIRO_TRY(ensure_tvals(plan, true));
+    SHIRO_TRY(ensure_tdvals(plan, 1, true));
+  }
   const int rc = fill_transposed(plan, s);
   if (rc != SHIRO_OK) {  // nothing is kept unless every step succeeds
     for (void* p : {(void*)tr.ptr, (void*)tr.row, (void*)tr.perm, (void*)tr.rid, (void*)tr.stage_of_csr,

@@ -133,6 +133,25 @@ def _check_large(shiro, plan, case):
     assert torch.equal(dvals, G[rows, 0] * B[col.reshape(-1), 0])
 
 
+def test_large_pattern_without_memory_for_the_staged_order(shiro):
+    """The staged value order is an optimisation: with memory for the direct
+    permutation only (row ids, the transposed pattern's three arrays, values
+    and gradients: 24 bytes a nonzero beside the work lists) prepare succeeds
+    and the gradients are the same."""
+    case = _large()
+    row_ptr, col, vals, _, _ = case
+    n, nnz = col.shape[0], vals.numel()
+    with arena(shiro) as a:
+        plan = shiro.partition(row_ptr, col.reshape(-1).int(), n, n, 1, 0)
+        shiro.select_rows(plan)
+        limit = a.held() + 24 * nnz + 8 * n + (16 << 20)
+        a.refuse = lambda b: a.held() + b > limit
+        shiro.prepare(plan, 1)
+        _check_large(shiro, plan, case)
+        plan.close()
+        assert not a.live
+
+
 def test_large_pattern_setup_memory(shiro):
     """Preparing a pattern in the staged order allocates one array (4 bytes a
     nonzero) more than the direct permutation needs, gives no large block back
