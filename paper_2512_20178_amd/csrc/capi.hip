@@ -224,6 +224,16 @@ int ensure_tdvals(shiro_plan plan, int tiles, bool allocate) {
   return SHIRO_OK;
 }
 
+int reserve_tdvals(shiro_plan plan, int tiles, bool allocate) {
+  if (tiles >= plan->tdvals_refused) tiles = 1;
+  int rc = ensure_tdvals(plan, tiles, allocate);
+  if (rc == SHIRO_ERR_OOM && tiles > 1) {
+    plan->tdvals_refused = tiles;
+    rc = ensure_tdvals(plan, 1, allocate);
+  }
+  return rc;
+}
+
 // Rows, nonzeros and distinct gathered rows of the pattern a kernel walks
 // (0 rows where the structures are not built yet; every one is fixed by the
 // panel's pattern, so a plan's defaults do not change once they are).
@@ -1013,7 +1023,7 @@ SHIRO_API int shiro_prepare(shiro_plan plan, int32_t N, shiro_dtype dt, uint32_t
   if (ops & SHIRO_OP_BACKWARD) {
     const shiro_tuning_t t = tuning_for(plan, SHIRO_KERNEL_SPMM_T, N, dt);
     SHIRO_TRY(ensure_tvals(plan, true));
-    SHIRO_TRY(ensure_tdvals(plan, is_walk(t) ? std::max(walk_dot_tiles(N, dt, t), 1) : 1, true));
+    SHIRO_TRY(reserve_tdvals(plan, is_walk(t) ? std::max(walk_dot_tiles(N, dt, t), 1) : 1, true));
     SHIRO_TRY(build_transposed(plan, s));
     SHIRO_TRY(ensure_cols_work(plan, t.chunk, true, s, &wl));
     SHIRO_TRY(ensure_carry(plan, (int64_t)wl->W * 2 * N, true));
@@ -1022,7 +1032,7 @@ SHIRO_API int shiro_prepare(shiro_plan plan, int32_t N, shiro_dtype dt, uint32_t
     const shiro_tuning_t t2 = tuning_for(plan, SHIRO_KERNEL_SDDMM, N, dt);
     SHIRO_TRY(ensure_rows_work(plan, t2.chunk, true, s, &wl));
     SHIRO_TRY(ensure_row_rid(plan, true, s));
-    SHIRO_TRY(ensure_tdvals(plan, walk_dot_tiles(N, dt, t2), true));
+    SHIRO_TRY(reserve_tdvals(plan, walk_dot_tiles(N, dt, t2), true));
   }
   if (ops & SHIRO_OP_ROW_BASED) {
     SHIRO_TRY(build_rowbased(plan, s));

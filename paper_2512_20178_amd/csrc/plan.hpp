@@ -159,6 +159,7 @@ struct shiro_plan_s {
   float* tvals = nullptr;
   float* tdvals = nullptr;   // one set per column tile of the walk
   int32_t tdvals_tiles = 0;
+  int32_t tdvals_refused = 1 << 30;  // sets there was no memory for
 
   // float32 accumulator of the per-block mode when Y is bfloat16
   float* acc32 = nullptr;
@@ -316,6 +317,9 @@ int ensure_carry(shiro_plan plan, int64_t elems, bool allocate);
 int ensure_acc32(shiro_plan plan, int64_t elems, bool allocate);
 int ensure_tvals(shiro_plan plan, bool allocate);
 int ensure_tdvals(shiro_plan plan, int tiles, bool allocate);
+// The same, or one set where there is no memory for more (plan->tdvals_refused
+// then says from how many on): several tiles' dots then take a pass of their own.
+int reserve_tdvals(shiro_plan plan, int tiles, bool allocate);
 // The hot-row arrays of kernel SHIRO_KERNEL_SPMM or _SPMM_T for H slots
 // (setup: copies the index array to the host; NOT_READY/CAPTURING when
 // allocate is false and they are missing).

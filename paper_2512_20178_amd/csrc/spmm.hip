@@ -1615,7 +1615,11 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* val
   // dvals ride along when one column tile covers N, or (the walk) up to four
   // tiles, whose partial dots the scatter pass adds
   const int tiles = is_walk(t) ? walk_dot_tiles(N, dt, t) : 1;
-  const bool fuse = dvals && Bp && (is_walk(t) ? tiles > 0 : (int64_t)effective_lanes(64, N, v) * v >= N);
+  bool fuse = dvals && Bp && (is_walk(t) ? tiles > 0 : (int64_t)effective_lanes(64, N, v) * v >= N);
+  if (fuse && tiles > 1) {
+    SHIRO_TRY(reserve_tdvals(plan, tiles, !cap));
+    fuse = tiles < plan->tdvals_refused;
+  }
   // Small patterns: the walk reads the values (and writes one tile's dots)
   // through the permutation itself, two launches less (4096-vertex R-MAT,
   // 2^15 R-MAT of 0.47M nonzeros: 43 -> 37 us), unless the gradients replace
@@ -1691,13 +1695,15 @@ int launch_sddmm(shiro_plan plan, const shiro_tuning_t& t, const float*, const v
   const WorkList* wl;
   SHIRO_TRY(ensure_rows_work(plan, t.chunk, !cap, s, &wl));
   const int tiles = walk_dot_tiles(N, dt, t);
+  const bool direct = tiles == 1 && !plan->vmap;
   SpmmArgs w{};
   w.ldx = ldp;
   w.ldd = lddy;
-  if (tiles > 0 && strides_32(w, dt, dt)) {
+  // without a buffer for the tiles' dots: the row kernel, which needs none
+  const bool fits = tiles > 0 && strides_32(w, dt, dt) &&
+                    (direct || (reserve_tdvals(plan, tiles, !cap) == SHIRO_OK && plan->tdvals_tiles >= tiles));
+  if (fits) {
     SHIRO_TRY(ensure_row_rid(plan, !cap, s));
-    const bool direct = tiles == 1 && !plan->vmap;
-    if (!direct) SHIRO_TRY(ensure_tdvals(plan, tiles, !cap));
     w.ptr = plan->row_ptr;
     w.idx = plan->colmap;
     w.rid = plan->row_rid;

@@ -7,6 +7,7 @@ import contextlib
 import pytest
 import torch
 
+import oracle
 import synth
 
 pytestmark = pytest.mark.gpu
@@ -172,3 +173,32 @@ def test_large_pattern_setup_memory(shiro):
         _check_large(shiro, plan, case)
         plan.close()
         assert not a.live
+
+
+def test_several_tiles_without_memory_for_their_gradients(shiro):
+    """dvals over several column tiles keep one set of partial sums per tile;
+    with memory for one set only, the product and the value gradients run as
+    two passes instead of failing."""
+    A, N = synth.small_rmat(12, 16), 320
+    Ad = A.to(torch.device("cuda"))
+    plan = shiro.partition(Ad.row_ptr, Ad.col, A.n_rows, A.n_cols, 1, 0)
+    shiro.select_rows(plan)
+    want = _backward(shiro, plan, Ad.vals, N)
+    one = 4 * plan.info()["nnz"]
+    with arena(shiro) as a:
+        a.refuse = lambda b: b in (2 * one, 3 * one, 4 * one)
+        plan = shiro.partition(Ad.row_ptr, Ad.col, A.n_rows, A.n_cols, 1, 0)
+        shiro.select_rows(plan)
+        shiro.prepare(plan, N)
+        got = _backward(shiro, plan, Ad.vals, N)
+        plan.close()
+        assert not a.live
+    assert torch.equal(got[0], want[0])
+    # float32 dots of 320 terms, componentwise against |dY||B|
+    Bp = synth.dense(len(want[0]), N, 1, synth.STREAM_B).numpy()
+    G = synth.dense(A.n_rows, N, 2, synth.STREAM_DY).numpy()
+    Ac = oracle.Csr.from_synth(A)
+    cm = oracle.select(Ac)[2]
+    ref, den = oracle.sddmm(Ac, G, Bp, cm), oracle.sddmm(Ac, G, Bp, cm, abs_mode=True)
+    for dv in (want[1], got[1]):
+        assert oracle.rel_err(dv.cpu().numpy(), ref, den) <= 1e-5
