@@ -120,7 +120,7 @@ bool stream_capturing(hipStream_t s) {
 
 void retire_buffer(shiro_plan plan, void* p) {
   if (!p) return;
-  if (plan->graphs.empty()) dev_free(p);
+  if (plan->graphs.empty() && !plan->captured) dev_free(p);
   else plan->retired.push_back(p);
 }
 
@@ -183,6 +183,7 @@ int ensure_cols_work(shiro_plan plan, int32_t chunk, bool allocate, hipStream_t 
 }
 
 int ensure_carry(shiro_plan plan, int64_t elems, bool allocate) {
+  if (!allocate) plan->captured = true;
   if (plan->carry_elems >= elems) return SHIRO_OK;
   if (!allocate) return set_error(SHIRO_ERR_CAPTURING, "carry buffer not prepared before capture");
   SHIRO_HIP(hipDeviceSynchronize());
@@ -195,6 +196,7 @@ int ensure_carry(shiro_plan plan, int64_t elems, bool allocate) {
 }
 
 int ensure_acc32(shiro_plan plan, int64_t elems, bool allocate) {
+  if (!allocate) plan->captured = true;
   if (plan->acc32_elems >= elems) return SHIRO_OK;
   if (!allocate) return set_error(SHIRO_ERR_CAPTURING, "per-block accumulator not prepared before capture");
   SHIRO_HIP(hipDeviceSynchronize());
@@ -207,12 +209,14 @@ int ensure_acc32(shiro_plan plan, int64_t elems, bool allocate) {
 }
 
 int ensure_tvals(shiro_plan plan, bool allocate) {
+  if (!allocate) plan->captured = true;
   if (plan->tvals) return SHIRO_OK;
   if (!allocate) return set_error(SHIRO_ERR_CAPTURING, "transposed values buffer not prepared before capture");
   return dev_alloc_n(&plan->tvals, std::max<int64_t>(plan->nnz, 1));
 }
 
 int ensure_tdvals(shiro_plan plan, int tiles, bool allocate) {
+  if (!allocate) plan->captured = true;
   if (plan->tdvals_tiles >= tiles) return SHIRO_OK;
   if (!allocate) return set_error(SHIRO_ERR_CAPTURING, "value gradients buffer not prepared before capture");
   SHIRO_HIP(hipDeviceSynchronize());
@@ -827,7 +831,9 @@ SHIRO_API int shiro_refresh_selection(shiro_plan plan, shiro_stream_t stream) {
   TraceRange range_("shiro.select_rows(refresh)");
   if (!plan) return set_error(SHIRO_ERR_INVALID_ARG, "refresh_selection: plan is NULL");
   if (!plan->selected) return set_error(SHIRO_ERR_NOT_READY, "refresh_selection: call shiro_select_rows first");
-  return run_select(plan, reinterpret_cast<hipStream_t>(stream), false);
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  if (stream_capturing(s)) plan->captured = true;
+  return run_select(plan, s, false);
 }
 
 SHIRO_API int shiro_plan_selection(shiro_plan plan, const int32_t** d_unique_cols,

@@ -172,9 +172,11 @@ struct shiro_plan_s {
 
   std::map<shiro::TuneKey, shiro_tuning_t> tuning;
   std::vector<hipGraphExec_t> graphs;
-  // buffers replaced by larger ones after a graph was captured: a captured
-  // graph may still name them, so they are freed with the plan only
+  // buffers replaced by larger ones after a graph was captured, by this library
+  // or by the caller (a call saw its stream capturing): a captured graph may
+  // still name them, so they are freed with the plan only
   std::vector<void*> retired;
+  bool captured = false;
   hipGraph_t capture_graph = nullptr;
 };
 

@@ -202,3 +202,50 @@ def test_several_tiles_without_memory_for_their_gradients(shiro):
     ref, den = oracle.sddmm(Ac, G, Bp, cm), oracle.sddmm(Ac, G, Bp, cm, abs_mode=True)
     for dv in (want[1], got[1]):
         assert oracle.rel_err(dv.cpu().numpy(), ref, den) <= 1e-5
+
+
+def test_buffers_of_a_captured_graph_stay(shiro):
+    """A graph captured by the caller (not by the library) holds the plan's
+    buffers by address.  Later calls that need larger ones leave those alone,
+    and the replay still gives the captured call's results."""
+    A, N = synth.small_rmat(11, 16), 130
+    dev = torch.device("cuda")
+    Ad = A.to(dev)
+    with arena(shiro) as a:
+        plan = shiro.partition(Ad.row_ptr, Ad.col, A.n_rows, A.n_cols, 1, 0)
+        U, _ = shiro.select_rows(plan)
+        shiro.prepare(plan, N)
+        Bp = synth.dense(U, N, 1, synth.STREAM_B).to(dev)
+        G = synth.dense(A.n_rows, N, 2, synth.STREAM_DY).to(dev)
+        Y = torch.empty(A.n_rows, N, device=dev)
+        dBp, dvals = torch.empty(U, N, device=dev), torch.empty(A.nnz, device=dev)
+
+        def step():
+            shiro.spmm(plan, Ad.vals, Bp, out=Y)
+            shiro.spmm_backward(plan, Ad.vals, G, Bp, dBpacked=dBp, dvals=dvals)
+
+        step()
+        torch.cuda.synchronize()
+        want = [t.clone() for t in (Y, dBp, dvals)]
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            step()
+        torch.cuda.synchronize()
+        at_capture = set(a.live)
+        for wider in (260, 520):  # larger carry slots, more sets of partial dots
+            shiro.prepare(plan, wider)
+            _backward(shiro, plan, Ad.vals, wider)
+        torch.cuda.synchronize()
+        gone = at_capture - set(a.live)
+        assert not gone, f"{len(gone)} blocks given back under a captured graph"
+        for _ in range(3):
+            for t in (Y, dBp, dvals):
+                t.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            for t, w in zip((Y, dBp, dvals), want):
+                assert torch.equal(t, w)
+            _backward(shiro, plan, Ad.vals, 64)  # eager work between the replays
+        del graph
+        plan.close()
+        assert not a.live
