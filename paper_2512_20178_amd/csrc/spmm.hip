@@ -1393,11 +1393,12 @@ int launch_pattern(shiro_plan plan, const shiro_tuning_t& t, const WorkList* wl,
 
 // The plan's values in its own nonzero order: the caller's array at the
 // panel's offset, or (subset plans) gathered through the value map.
-static const float* plan_values(shiro_plan plan, const float* vals, hipStream_t s) {
-  const float* v = vals + plan->nz_begin;
-  if (!plan->vmap || plan->nnz == 0) return v;
-  (void)gather_values(plan->vmap, v, plan->nnz, plan->svals, s);  // the caller checks the launch
-  return plan->svals;
+static int plan_values(shiro_plan plan, const float* vals, const float** out, hipStream_t s) {
+  *out = vals + plan->nz_begin;
+  if (!plan->vmap || plan->nnz == 0) return SHIRO_OK;
+  SHIRO_TRY(gather_values(plan->vmap, *out, plan->nnz, plan->svals, s));
+  *out = plan->svals;
+  return SHIRO_OK;
 }
 
 int ensure_hot(shiro_plan plan, int kernel, int32_t H, bool allocate, hipStream_t s, const HotRows** out) {
@@ -1475,8 +1476,8 @@ int launch_spmm(shiro_plan plan, const shiro_tuning_t& t, const float* vals, con
   const HotRows* hot = nullptr;
   if (t.group_rows == 3 && t.lds_rows > 0)
     SHIRO_TRY(ensure_hot(plan, SHIRO_KERNEL_SPMM, t.lds_rows, !stream_capturing(s), s, &hot));
-  const float* v = plan_values(plan, vals, s);
-  SHIRO_LAUNCH_CHECK();
+  const float* v;
+  SHIRO_TRY(plan_values(plan, vals, &v, s));
   return launch_pattern(plan, t, wl, plan->row_ptr, plan->colmap, v, plan->rows, X, plan->U, ldx, N, in_dt, Y, ldy,
                         out_dt, s, nullptr, t.group_rows >= 1 ? plan->row_rid : nullptr, nullptr, hot);
 }
@@ -1502,8 +1503,8 @@ int launch_spmm_fixed(shiro_plan plan, const shiro_tuning_t& t, const float* val
       return set_error(SHIRO_ERR_NOT_READY, "spmm_noalloc: LDS rows of the tuning not built; run shiro_prepare first");
     hot = &ht->second;
   }
-  const float* v = plan_values(plan, vals, s);
-  SHIRO_LAUNCH_CHECK();
+  const float* v;
+  SHIRO_TRY(plan_values(plan, vals, &v, s));
   return launch_pattern(plan, t, wl, plan->row_ptr, plan->colmap, v, plan->rows, X, plan->U, ldx, N, in_dt, Y, ldy,
                         out_dt, s, nullptr, t.group_rows >= 1 ? plan->row_rid : nullptr, carry, hot);
 }

@@ -249,3 +249,37 @@ def test_buffers_of_a_captured_graph_stay(shiro):
         del graph
         plan.close()
         assert not a.live
+
+
+def test_launch_errors_of_subset_plans_are_reported(shiro):
+    """An error the runtime holds when a product is launched is reported by
+    the call, on plans that gather their values first as on the others."""
+    import ctypes
+
+    A, N = synth.small_rmat(8, 8), 16
+    dev = torch.device("cuda")
+    Ad = A.to(dev)
+    hip = ctypes.CDLL("libamdhip64.so")
+    L = shiro._L()
+    keep = torch.ones(A.nnz, dtype=torch.uint8, device=dev)
+    codes = []
+    for subset in (False, True):
+        if subset:
+            plan = shiro.partition_subset(Ad.row_ptr, Ad.col, A.n_rows, A.n_cols, 1, 0, keep, 1)
+        else:
+            plan = shiro.partition(Ad.row_ptr, Ad.col, A.n_rows, A.n_cols, 1, 0)
+        U, _ = shiro.select_rows(plan)
+        shiro.prepare(plan, N)
+        Bp = synth.dense(U, N, 1, synth.STREAM_B).to(dev)
+        Y = torch.empty(A.n_rows, N, device=dev)
+        args = (plan.handle, Ad.vals.data_ptr(), Bp.data_ptr(), N, N, shiro._lib.F32, Y.data_ptr(), N,
+                shiro._lib.F32, shiro._lib.MODE_BATCHED, shiro._stream())
+        torch.cuda.synchronize()
+        assert L.shiro_spmm(*args) == 0
+        torch.cuda.synchronize()
+        assert hip.hipSetDevice(9999) != 0  # leaves an error for the next check
+        codes.append(L.shiro_spmm(*args))
+        hip.hipGetLastError()
+        torch.cuda.synchronize()
+        plan.close()
+    assert codes[0] == codes[1]
