@@ -1050,11 +1050,16 @@ int run_walk(const shiro_tuning_t& t, shiro_dtype in_dt, shiro_dtype out_dt, Spm
 }
 
 // The walk holds row strides in 32 bits (bytes); rows further apart take the
-// row kernel.
+// row kernel.  So do widths of more column tiles than a grid may have in y:
+// the row kernel's widest tiles are twice as wide.
 bool strides_32(const SpmmArgs& a, shiro_dtype in_dt, shiro_dtype out_dt) {
   const int64_t in = in_dt == SHIRO_F32 ? 4 : 2, out = out_dt == SHIRO_F32 ? 4 : 2;
   const int64_t lim = (int64_t)1 << 32;
   return a.ldx * in < lim && a.ldd * in < lim && a.ldo * out < lim && a.lds * out < lim;
+}
+
+bool walk_fits(const SpmmArgs& a, shiro_dtype in_dt, shiro_dtype out_dt, const shiro_tuning_t& t) {
+  return strides_32(a, in_dt, out_dt) && ceil_div(a.N, (int64_t)kWave * walk_vec(a.N, in_dt, t.lanes)) <= 65535;
 }
 
 template <typename TIN, typename TOUT>
@@ -1065,9 +1070,10 @@ int run_spmm_family(shiro_plan plan, shiro_tuning_t t, const WorkList* wl, SpmmA
   constexpr shiro_dtype in_dt = std::is_same<TIN, float>::value ? SHIRO_F32 : SHIRO_BF16;
   constexpr shiro_dtype out_dt = std::is_same<TOUT, float>::value ? SHIRO_F32 : SHIRO_BF16;
   unsigned nb;
-  if (is_walk(t) && a.rid && strides_32(a, in_dt, out_dt)) {
+  if (is_walk(t) && a.rid && walk_fits(a, in_dt, out_dt, t)) {
     SHIRO_TRY(run_walk(t, in_dt, out_dt, a, s));
   } else {
+    if (is_walk(t)) t.lanes = 64;
     t.lanes = effective_lanes(t.lanes, a.N, vec);
     // the windowed walk gives each lane group its own chunks
     const int32_t workers = (t.group_rows == 3 && a.rid) ? kWavesPerBlock * (kWave / t.lanes) : kWavesPerBlock;
@@ -1602,7 +1608,10 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* val
   a.X = dY;
   a.x_rows = plan->rows;
   a.N = N;
-  if (is_walk(t) && !strides_32(a, dt, dt)) t.group_rows = 0;
+  if (is_walk(t) && !walk_fits(a, dt, dt, t)) {
+    t.group_rows = 0;
+    t.lanes = 64;
+  }
   if (!plan->tr.built) {
     if (cap) return set_error(SHIRO_ERR_CAPTURING, "backward: transposed pattern not prepared before capture");
     SHIRO_TRY(build_transposed(plan, s));
