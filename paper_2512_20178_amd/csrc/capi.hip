@@ -256,8 +256,8 @@ static void pattern_sizes(shiro_plan plan, int kernel, int64_t* rows, int64_t* n
   }
 }
 
-// Defaults from sweeps on MI355X: the nonzero walk for every kernel (the
-// sampled product has no other).
+// Defaults from sweeps on MI355X: the nonzero walk, except for the sampled
+// product where its last tile would be mostly idle.
 //
 // Chunk: at most 256 merge items (longer runs lengthen the serial sums and
 // the last round), fewer where that leaves the chip short of wavefronts: 256
@@ -276,7 +276,20 @@ static void pattern_sizes(shiro_plan plan, int kernel, int64_t* rows, int64_t* n
 // per row (2^24 panel, 3.4) or short rows (its backward, 3.4 nonzeros, 471
 // against 496 us) or cached matrices (2^16 R-MAT, 1M nonzeros, 47 against 51)
 // a second pass costs more than it saves.
-shiro_tuning_t default_tuning(shiro_plan plan, int kernel, int32_t N, shiro_dtype) {
+//
+// Sampled product (above 64 columns; below, dots.hip whatever the tuning):
+// the row kernel reads a row of whole 16-byte pieces in one pass, so the walk
+// loses to it where its last tile is mostly idle, and where rows are no whole
+// 128-byte lines, because the line at a tile's end is then read twice.  dvals
+// alone in us, row kernel / walk: 2^18 ER matrix (3.1M nonzeros, float32) N =
+// 136 317 / 423, 200 460 / 495, 256 (full tiles) 522 / 507; bfloat16 N = 264
+// 314 / 420, 512 510 / 491; panel of 2^22 R-MAT, N = 320 (5/6 full) 369 / 363.
+// On reused rows with 256-byte tiles those are what has to be full: 2^18 R-MAT
+// N = 192 331 / 257.  Rows that are no whole pieces: the walk (2^18 ER,
+// bfloat16 N = 260 677 / 438).  The row kernel has its own chunk, lanes, depth
+// and grid: with those of the walk 2^18 R-MAT took 585 to 2056 us instead of
+// 510 to 1471 at N = 288 to 511.
+shiro_tuning_t default_tuning(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt) {
   shiro_tuning_t t;
   t.lanes = 32;
   t.unroll = 4;
@@ -289,7 +302,23 @@ shiro_tuning_t default_tuning(shiro_plan plan, int kernel, int32_t N, shiro_dtyp
   const int64_t chunks = std::min<int64_t>(16384, (1 << 22) / std::max(N, 1));
   const int64_t c = ceil_div(rows + nnz, std::max<int64_t>(chunks, 1));
   t.chunk = (int32_t)std::min<int64_t>(256, std::max<int64_t>(16, ceil_div(c, 16) * 16));
-  if (nnz >= (1 << 21) && nnz >= 12 * rows && nnz >= 12 * gathered) t.lanes = 16;
+  const bool reused = nnz >= (1 << 21) && nnz >= 12 * rows && nnz >= 12 * gathered;
+  if (reused) t.lanes = 16;
+  if (kernel == SHIRO_KERNEL_SDDMM) {
+    const int64_t unit = dt == SHIRO_F32 ? 1 : 2;                  // elements in 4 bytes
+    const int64_t half = 64 * unit, tile = 128 * unit;             // columns of 256 and 512 bytes
+    const bool pieces = N % (4 * unit) == 0, lines = N % (32 * unit) == 0;
+    const bool full16 = reused && lines && N <= 4 * half;
+    const bool full32 = N <= tile || !pieces || (lines && 5 * N >= 4 * tile * ceil_div((int64_t)N, tile));
+    if (!full16 || N < tile) t.lanes = 32;
+    if (!full16 && (!full32 || N > 4 * tile)) {
+      t.group_rows = 0;
+      t.chunk = std::min(t.chunk, 128);
+      t.lanes = 64;
+      t.unroll = 2;
+      t.wg_per_cu = 8;
+    }
+  }
   return t;
 }
 
@@ -303,7 +332,7 @@ int validate_tuning(int kernel, int32_t N, shiro_dtype dt, const shiro_tuning_t&
     return set_error(SHIRO_ERR_INVALID_ARG, "tuning: unroll must be 1, 2 or 4");
   if (t.group_rows < 0 || t.group_rows > 3) return set_error(SHIRO_ERR_INVALID_ARG, "tuning: group_rows must be 0, 1, 2 or 3");
   if (t.group_rows >= 2 && kernel == SHIRO_KERNEL_SDDMM)
-    return set_error(SHIRO_ERR_INVALID_ARG, "tuning: the sampled product has no nonzero walk (group_rows 0 or 1)");
+    return set_error(SHIRO_ERR_INVALID_ARG, "tuning: the sampled product has group_rows 0 (row kernel) and 1 (nonzero walk)");
   if (t.xcd_remap != 0 && t.xcd_remap != 1) return set_error(SHIRO_ERR_INVALID_ARG, "tuning: xcd_remap must be 0 or 1");
   if (t.wg_per_cu < 1 || t.wg_per_cu > 32) return set_error(SHIRO_ERR_INVALID_ARG, "tuning: wg_per_cu outside [1, 32]");
   if (t.lds_rows < 0 || t.lds_rows > 128) return set_error(SHIRO_ERR_INVALID_ARG, "tuning: lds_rows outside [0, 128]");

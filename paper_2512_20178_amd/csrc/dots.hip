@@ -6,9 +6,11 @@
 // wavefront takes a window of 64 consecutive nonzeros (one coalesced load of
 // their indices and row ids), 64 / L at a time, both dense rows gathered, and
 // stores the window's dots together.  No work list: 256 nonzeros a wavefront.
+// Four columns a lane, one below 4 columns (a row is then shorter than a lane).
 // Bound by its gathers' L2 requests. dvals alone, us, wavefront-per-row kernel /
-// walk / this: 2^18 R-MAT (4.9M nonzeros) at N = 32 183 / 109 / 49, ER panel
-// (4.2M) at N = 16 in bfloat16 95 / 113 / 89, 2^19 R-MAT (15.5M) at N = 64
+// walk / this: 2^18 R-MAT (4.9M nonzeros) at N = 32 183 / 109 / 49, at N = 1
+// 140 / 84 / 27; 2^18 ER (3.1M) at N = 3 in bfloat16 65 / 96 / 24; ER panel
+// (4.2M) at N = 16 in bfloat16 95 / 113 / 89; 2^19 R-MAT (15.5M) at N = 64
 // 710 / 342 / 334; from 65 columns on the walk's gathers are full wavefronts.
 #include "plan.hpp"
 #include "walk.hpp"
@@ -73,7 +75,8 @@ int go(const int32_t* idx, const int32_t* rid, const void* D, int64_t ldd, const
        const int32_t* map, float* out, int64_t nnz, int32_t N, hipStream_t s) {
   const int64_t blocks = ceil_div(nnz, (int64_t)kWave * kDotWindows * kWavesPerBlock);
   const TIN *d = reinterpret_cast<const TIN*>(D), *x = reinterpret_cast<const TIN*>(X);
-  if (N <= 32) k_dots<TIN, 8, 4><<<dim3((unsigned)blocks), kBlock, 0, s>>>(idx, rid, d, ldd, x, ldx, map, out, nnz, N);
+  if (N < 4) k_dots<TIN, 8, 1><<<dim3((unsigned)blocks), kBlock, 0, s>>>(idx, rid, d, ldd, x, ldx, map, out, nnz, N);
+  else if (N <= 32) k_dots<TIN, 8, 4><<<dim3((unsigned)blocks), kBlock, 0, s>>>(idx, rid, d, ldd, x, ldx, map, out, nnz, N);
   else k_dots<TIN, 16, 4><<<dim3((unsigned)blocks), kBlock, 0, s>>>(idx, rid, d, ldd, x, ldx, map, out, nnz, N);
   SHIRO_LAUNCH_CHECK();
   return SHIRO_OK;
@@ -81,12 +84,12 @@ int go(const int32_t* idx, const int32_t* rid, const void* D, int64_t ldd, const
 
 }  // namespace
 
-bool dots_narrow(int32_t N) { return N >= 4 && N <= 64; }
+bool dots_narrow(int32_t N) { return N >= 1 && N <= 64; }
 
 int launch_dots(const int32_t* idx, const int32_t* rid, const void* D, int64_t ldd, const void* X, int64_t ldx,
                 const int32_t* map, float* out, int64_t nnz, int32_t N, shiro_dtype dt, hipStream_t s) {
   if (nnz <= 0) return SHIRO_OK;
-  if (!dots_narrow(N)) return set_error(SHIRO_ERR_UNSUPPORTED, "dots: 4 to 64 columns");
+  if (!dots_narrow(N)) return set_error(SHIRO_ERR_UNSUPPORTED, "dots: 1 to 64 columns");
   if (dt == SHIRO_F32) return go<float>(idx, rid, D, ldd, X, ldx, map, out, nnz, N, s);
   return go<bf16_t>(idx, rid, D, ldd, X, ldx, map, out, nnz, N, s);
 }

@@ -599,103 +599,6 @@ __global__ __launch_bounds__(kBlock) void k_fixup(SHIRO_SPMM_PARAMS(TIN, TOUT),
 }
 
 // ---------------------------------------------------------------------------
-// SDDMM: dvals[k] = dY[row(k), :] . Bp[colmap[k], :]
-// ---------------------------------------------------------------------------
-struct SddmmArgs {
-  const int64_t* ptr;
-  const int32_t* idx;
-  const void* dY;
-  int64_t lddy;
-  const void* Bp;
-  int64_t ldp;
-  float* dvals;
-  const int32_t* out_map;  // optional: dvals index of each pattern nonzero (subset plans)
-  const int32_t* chunk_row;
-  const int32_t* chunk_nz;
-  int32_t W, R, N;
-  int32_t chunks_per_wave;
-  int32_t xcd_remap;
-};
-
-template <typename TIN, int LANES, int VEC, int UNROLL>
-__global__ __launch_bounds__(kBlock) void k_sddmm(
-    const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx, const TIN* __restrict__ dY,
-    int64_t lddy, const TIN* __restrict__ Bp, int64_t ldp, float* __restrict__ dvals,
-    const int32_t* __restrict__ out_map, const int32_t* __restrict__ chunk_row,
-    const int32_t* __restrict__ chunk_nz, int32_t W, int32_t R, int32_t N, int32_t cpw, int32_t xcd_remap) {
-  constexpr int G = kWave / LANES;
-  constexpr int TW = LANES * VEC;
-  constexpr int STEP = G * UNROLL;
-  const int lane = lane_id();
-  const int g = lane / LANES;
-  const int li = lane % LANES;
-  const int ntiles = (N + TW - 1) / TW;
-  const int64_t c0 = (int64_t)li * VEC;
-
-  const int32_t gw = uniform(logical_block(xcd_remap) * kWavesPerBlock + wave_id());
-  const int32_t w_begin = gw * cpw;
-  const int32_t w_end = min(w_begin + cpw, W);
-
-  for (int32_t w = w_begin; w < w_end; ++w) {
-    const int32_t i0 = chunk_row[w], i1 = chunk_row[w + 1];
-    const int64_t j0 = chunk_nz[w], j1 = chunk_nz[w + 1];
-    int64_t rs = i0 < R ? ptr[i0] : 0;
-    for (int32_t r = i0; r <= i1 && r < R; ++r) {
-      const int64_t re = ptr[r + 1];
-      const int64_t kb = rs > j0 ? rs : j0;
-      const int64_t ke = re < j1 ? re : j1;
-      rs = re;
-      if (kb >= ke) continue;
-      // first column tile of dY row r stays in registers for the whole row
-      float y0[VEC];
-      Elem<TIN>::template load<VEC>(dY + (int64_t)r * lddy + (c0 < N ? c0 : 0), y0);
-      if (c0 >= N) {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) y0[e] = 0.f;
-      }
-      for (int64_t k = kb; k < ke; k += STEP) {
-        int32_t xi[UNROLL];
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-          const int64_t kk = k + u * G + g;
-          xi[u] = idx[kk < ke ? kk : ke - 1];
-        }
-        float part[UNROLL];
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-          float b[VEC];
-          Elem<TIN>::template load<VEC>(Bp + (int64_t)xi[u] * ldp + (c0 < N ? c0 : 0), b);
-          part[u] = 0.f;
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) part[u] = fmaf(y0[e], b[e], part[u]);
-        }
-        for (int t = 1; t < ntiles; ++t) {
-          const int64_t ct = (int64_t)t * TW + c0;
-          const bool cv = ct < N;
-          float y[VEC];
-          Elem<TIN>::template load<VEC>(dY + (int64_t)r * lddy + (cv ? ct : 0), y);
-#pragma unroll
-          for (int u = 0; u < UNROLL; ++u) {
-            float b[VEC];
-            Elem<TIN>::template load<VEC>(Bp + (int64_t)xi[u] * ldp + (cv ? ct : 0), b);
-            float q = 0.f;
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) q = fmaf(y[e], b[e], q);
-            part[u] += cv ? q : 0.f;
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-          part[u] = group_sum<LANES>(part[u]);
-          const int64_t kk = k + u * G + g;
-          if (li == LANES - 1 && kk < ke) dvals[out_map ? (int64_t)out_map[kk] : kk] = part[u];
-        }
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // pack: Bp[u, :] = B[uc[u], :]  (bit-exact row gather)
 // ---------------------------------------------------------------------------
 template <typename T, int LANES, int VEC, int UNROLL>
@@ -1010,18 +913,6 @@ int spmm_dispatch(const shiro_tuning_t& t, dim3 grid, hipStream_t s, const SpmmA
   SHIRO_SPMM_CASE(64, 1) SHIRO_SPMM_CASE(64, 2) SHIRO_SPMM_CASE(64, 4)
 #undef SHIRO_SPMM_CASE
   return set_error(SHIRO_ERR_UNSUPPORTED, "spmm: no kernel for lanes/unroll");
-}
-
-template <typename TIN, int VEC>
-int run_sddmm(shiro_plan plan, const WorkList* wl, SddmmArgs a, hipStream_t s) {
-  shiro_tuning_t t = default_tuning(plan, SHIRO_KERNEL_SDDMM, a.N, SHIRO_F32);
-  unsigned nb;
-  SHIRO_TRY(grid_waves(plan, t, wl->W, kWavesPerBlock, &a.chunks_per_wave, &nb));
-  k_sddmm<TIN, 64, VEC, 2><<<dim3(nb), kBlock, 0, s>>>(
-      a.ptr, a.idx, reinterpret_cast<const TIN*>(a.dY), a.lddy, reinterpret_cast<const TIN*>(a.Bp), a.ldp, a.dvals,
-      a.out_map, a.chunk_row, a.chunk_nz, a.W, a.R, a.N, a.chunks_per_wave, 0);
-  SHIRO_LAUNCH_CHECK();
-  return SHIRO_OK;
 }
 
 // Lanes actually used: never more than one column tile needs.
@@ -1686,12 +1577,11 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* val
 }
 
 // Up to 64 columns: dots.hip.  Wider: the walk over the panel's own pattern,
-// dots only: dY row i stays in
-// registers while the wavefront gathers the Bpacked rows of its nonzeros.
-// One tile of a whole panel writes the gradients in place, otherwise the
-// tiles' partial dots are summed (through the value map of a subset plan).
-// The wavefront-per-row kernel (710 against 342 us for 15.5M nonzeros of a
-// 2^19 R-MAT at N = 64) stays for more than four tiles and rows 4 GB apart.
+// dots only (group_rows 1): dY row i stays in registers while the wavefront
+// gathers the Bpacked rows of its nonzeros.  One tile of a whole panel writes
+// the gradients in place, otherwise the tiles' partial dots are summed (through
+// the value map of a subset plan).  Or the row kernel (group_rows 0; also where
+// the walk has more than four tiles, rows 4 GB apart or no buffer for its dots).
 int launch_sddmm(shiro_plan plan, const shiro_tuning_t& t, const float*, const void* dY,
                  int64_t lddy, const void* Bp, int64_t ldp, int32_t N, shiro_dtype dt,
                  float* dvals, hipStream_t s) {
@@ -1710,7 +1600,7 @@ int launch_sddmm(shiro_plan plan, const shiro_tuning_t& t, const float*, const v
   w.ldx = ldp;
   w.ldd = lddy;
   // without a buffer for the tiles' dots: the row kernel, which needs none
-  const bool fits = tiles > 0 && strides_32(w, dt, dt) &&
+  const bool fits = is_walk(t) && tiles > 0 && strides_32(w, dt, dt) &&
                     (direct || (reserve_tdvals(plan, tiles, !cap) == SHIRO_OK && plan->tdvals_tiles >= tiles));
   if (fits) {
     SHIRO_TRY(ensure_row_rid(plan, !cap, s));
@@ -1745,12 +1635,18 @@ int launch_sddmm(shiro_plan plan, const shiro_tuning_t& t, const float*, const v
   a.W = wl->W;
   a.R = (int32_t)plan->rows;
   a.N = N;
-  if (dt == SHIRO_F32) {
-    if (vec_for<float>(N, {{dY, lddy}, {Bp, ldp}}) == 4) return run_sddmm<float, 4>(plan, wl, a, s);
-    return run_sddmm<float, 1>(plan, wl, a, s);
+  shiro_tuning_t r = t;
+  if (is_walk(t)) {  // the knobs of a walk that does not fit say nothing here
+    r.lanes = 64;
+    r.unroll = 2;
+    r.wg_per_cu = 8;
   }
-  if (vec_for<bf16_t>(N, {{dY, lddy}, {Bp, ldp}}) == 8) return run_sddmm<bf16_t, 8>(plan, wl, a, s);
-  return run_sddmm<bf16_t, 1>(plan, wl, a, s);
+  const int v = dt == SHIRO_F32 ? vec_for<float>(N, {{dY, lddy}, {Bp, ldp}}) : vec_for<bf16_t>(N, {{dY, lddy}, {Bp, ldp}});
+  r.lanes = effective_lanes(r.lanes, N, v);
+  a.xcd_remap = r.xcd_remap;
+  unsigned nb;
+  SHIRO_TRY(grid_waves(plan, r, wl->W, kWavesPerBlock, &a.chunks_per_wave, &nb));
+  return launch_sddmm_rows(a, dt, v, r.lanes, r.unroll, dim3(nb), s);
 }
 
 // Per-block structures (setup): each column block's own CSR over its (row,

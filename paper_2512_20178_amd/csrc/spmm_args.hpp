@@ -78,6 +78,24 @@ inline bool walk_narrow(const SpmmArgs& a, int64_t size, int vec) {
          vec * size >= 4;
 }
 
+// The row kernel of the sampled product (sddmm.hip): dvals[k] = dY[row(k), :] . Bp[idx[k], :].
+struct SddmmArgs {
+  const int64_t* ptr;
+  const int32_t* idx;
+  const void* dY;
+  int64_t lddy;
+  const void* Bp;
+  int64_t ldp;
+  float* dvals;
+  const int32_t* out_map;  // optional: dvals index of each pattern nonzero (subset plans)
+  const int32_t* chunk_row;
+  const int32_t* chunk_nz;
+  int32_t W, R, N;
+  int32_t chunks_per_wave;
+  int32_t xcd_remap;
+};
+int launch_sddmm_rows(const SddmmArgs& a, shiro_dtype dt, int vec, int lanes, int unroll, dim3 grid, hipStream_t s);
+
 // The nonzero walk (walk_*.hip).  The grid covers a.W chunks, a.chunks_per_wave
 // consecutive ones per wavefront, and `tiles` column tiles of 64 * vec columns.
 int launch_walk_f32(const SpmmArgs& a, int vec, dim3 grid, hipStream_t s);

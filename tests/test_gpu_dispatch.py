@@ -59,3 +59,34 @@ def test_more_column_tiles_than_a_grid_holds(shiro):
     dBp = torch.empty_like(Bp)
     shiro.spmm_backward(plan, vals, Y, None, dBpacked=dBp)
     assert torch.equal(dBp, torch.stack([2 * Y[0], 3 * Y[2], -Y[0]]))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("N", [1, 2, 3, 72, 136, 200, 260, 264, 513, 520, 1030])
+def test_sampled_product_kernels(shiro, N, dtype):
+    """dvals alone: by default (lane groups up to 64 columns, the walk where
+    its tiles are full or rows are no whole 16-byte pieces, else the row
+    kernel), and with either kernel asked for, whose knobs then count."""
+    A = _pattern(150, 200, N)
+    plan, U, Ad = _plan(shiro, A)
+    Ac = oracle.Csr.from_synth(A)
+    B = synth.dense(A.n_cols, N, N, synth.STREAM_B).to(dtype)
+    G = synth.dense(A.n_rows, N, N, synth.STREAM_DY).to(dtype)
+    Bn, Gn = B.float().numpy(), G.float().numpy()
+    ref, den = oracle.sddmm(Ac, Gn, Bn, None), oracle.sddmm(Ac, Gn, Bn, None, abs_mode=True)
+    default = shiro.get_tuning(plan, "sddmm", N, dtype)
+    if N > 64:
+        walk = N in (72, 513) if dtype == torch.float32 else N in (72, 136, 200, 260, 513)
+        walk &= not (dtype == torch.float32 and N == 513)  # five tiles
+        assert default["group_rows"] == int(walk)
+    knobs = [default, dict(default, group_rows=1, lanes=16), dict(default, group_rows=1, lanes=32)]
+    knobs += [dict(default, group_rows=0, lanes=lanes, unroll=u, wg_per_cu=w, chunk=c)
+              for lanes, u, w, c in ((8, 1, 1, 16), (16, 4, 32, 100), (32, 1, 2, 4096), (64, 2, 8, 128), (64, 4, 16, 64))]
+    for pad in (0, 1):
+        Bp = shiro.pack_B(plan, B.cuda(), out=torch.empty(U, N + pad, dtype=dtype, device="cuda")[:, :N])
+        Gd = torch.zeros(A.n_rows, N + pad, dtype=dtype, device="cuda")[:, :N].copy_(G)
+        for t in knobs:
+            shiro.set_tuning(plan, "sddmm", N, dtype, **t)
+            dvals = torch.full((A.nnz,), float("nan"), device="cuda")
+            shiro.spmm_backward(plan, None, Gd, Bp, dvals=dvals)
+            assert oracle.rel_err(dvals.cpu().numpy(), ref, den) <= 1e-5, (pad, t)
