@@ -275,7 +275,10 @@ static void pattern_sizes(shiro_plan plan, int kernel, int64_t* rows, int64_t* n
 // nonzeros a row) 188 -> 169 and 356 -> 328 us.  Otherwise 512: with few uses
 // per row (2^24 panel, 3.4) or short rows (its backward, 3.4 nonzeros, 471
 // against 496 us) or cached matrices (2^16 R-MAT, 1M nonzeros, 47 against 51)
-// a second pass costs more than it saves.
+// a second pass costs more than it saves; so it does for rows of less than 512
+// bytes, which one pass reads whole (2^19 normalised R-MAT, 8M nonzeros, N = 72:
+// forward 283 us in one pass, 375 in two, gradients 535 and 624; N = 100 380
+// and 455; bfloat16 N = 136 287 and 393).
 //
 // Sampled product (above 64 columns; below, dots.hip whatever the tuning):
 // the row kernel reads a row of whole 16-byte pieces in one pass, so the walk
@@ -284,8 +287,9 @@ static void pattern_sizes(shiro_plan plan, int kernel, int64_t* rows, int64_t* n
 // alone in us, row kernel / walk: 2^18 ER matrix (3.1M nonzeros, float32) N =
 // 136 317 / 423, 200 460 / 495, 256 (full tiles) 522 / 507; bfloat16 N = 264
 // 314 / 420, 512 510 / 491; panel of 2^22 R-MAT, N = 320 (5/6 full) 369 / 363.
-// On reused rows with 256-byte tiles those are what has to be full: 2^18 R-MAT
-// N = 192 331 / 257.  Rows that are no whole pieces: the walk (2^18 ER,
+// Reused rows gain more from the walk, whole lines or not, and with 256-byte
+// tiles those are what has to be full: 2^18 R-MAT N = 192 331 / 257, 240 450 /
+// 398, 176 321 / 295.  Rows that are no whole pieces: the walk (2^18 ER,
 // bfloat16 N = 260 677 / 438).  The row kernel has its own chunk, lanes, depth
 // and grid: with those of the walk 2^18 R-MAT took 585 to 2056 us instead of
 // 510 to 1471 at N = 288 to 511.
@@ -303,15 +307,17 @@ shiro_tuning_t default_tuning(shiro_plan plan, int kernel, int32_t N, shiro_dtyp
   const int64_t c = ceil_div(rows + nnz, std::max<int64_t>(chunks, 1));
   t.chunk = (int32_t)std::min<int64_t>(256, std::max<int64_t>(16, ceil_div(c, 16) * 16));
   const bool reused = nnz >= (1 << 21) && nnz >= 12 * rows && nnz >= 12 * gathered;
-  if (reused) t.lanes = 16;
+  const int64_t unit = dt == SHIRO_F32 ? 1 : 2;       // elements in 4 bytes
+  const int64_t half = 64 * unit, tile = 128 * unit;  // columns of 256 and 512 bytes
+  if (reused && N >= tile) t.lanes = 16;
   if (kernel == SHIRO_KERNEL_SDDMM) {
-    const int64_t unit = dt == SHIRO_F32 ? 1 : 2;                  // elements in 4 bytes
-    const int64_t half = 64 * unit, tile = 128 * unit;             // columns of 256 and 512 bytes
     const bool pieces = N % (4 * unit) == 0, lines = N % (32 * unit) == 0;
-    const bool full16 = reused && lines && N <= 4 * half;
-    const bool full32 = N <= tile || !pieces || (lines && 5 * N >= 4 * tile * ceil_div((int64_t)N, tile));
-    if (!full16 || N < tile) t.lanes = 32;
-    if (!full16 && (!full32 || N > 4 * tile)) {
+    auto fill = [&](int64_t w) { return 100 * N / (ceil_div((int64_t)N, w) * w); };  // per cent
+    const bool wide = N <= 4 * tile && (N <= tile || !pieces || ((lines || reused) && fill(tile) >= 78));
+    const bool narrow = reused && pieces && N >= tile && N <= 4 * half &&
+                        (lines || (!wide && N > tile && fill(half) >= 90));
+    t.lanes = narrow ? 16 : 32;
+    if (!narrow && !wide) {
       t.group_rows = 0;
       t.chunk = std::min(t.chunk, 128);
       t.lanes = 64;
@@ -1058,7 +1064,7 @@ SHIRO_API int shiro_prepare(shiro_plan plan, int32_t N, shiro_dtype dt, uint32_t
   if (ops & SHIRO_OP_BACKWARD) {
     const shiro_tuning_t t = tuning_for(plan, SHIRO_KERNEL_SPMM_T, N, dt);
     SHIRO_TRY(ensure_tvals(plan, true));
-    SHIRO_TRY(reserve_tdvals(plan, is_walk(t) ? std::max(walk_dot_tiles(N, dt, t), 1) : 1, true));
+    SHIRO_TRY(reserve_tdvals(plan, is_walk(t) ? std::max(walk_dot_tiles(N, dt, with_dots(t, N, dt)), 1) : 1, true));
     SHIRO_TRY(build_transposed(plan, s));
     SHIRO_TRY(ensure_cols_work(plan, t.chunk, true, s, &wl));
     SHIRO_TRY(ensure_carry(plan, (int64_t)wl->W * 2 * N, true));

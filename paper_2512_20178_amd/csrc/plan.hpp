@@ -344,6 +344,15 @@ inline int walk_dot_tiles(int32_t N, shiro_dtype dt, const shiro_tuning_t& t) {
   const int64_t n = ceil_div(N, (int64_t)kWave * walk_vec(N, dt, t.lanes));
   return n <= 4 ? (int)n : 0;
 }
+// The walk's tuning when it is asked for dots: 256-byte tiles become 512-byte
+// ones where only those are few enough to fuse, because dots on their own cost
+// a second pass over the gathered rows (2^18 R-MAT, N = 320 float32: 654 us
+// fused, 1169 with k_sddmm after 256-byte tiles).
+inline shiro_tuning_t with_dots(shiro_tuning_t t, int32_t N, shiro_dtype dt) {
+  shiro_tuning_t w = t;
+  w.lanes = 32;
+  return is_walk(t) && walk_dot_tiles(N, dt, t) == 0 && walk_dot_tiles(N, dt, w) > 0 ? w : t;
+}
 
 shiro_tuning_t default_tuning(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt);
 // The tuning a plan uses for one kernel family (its own, else the default).

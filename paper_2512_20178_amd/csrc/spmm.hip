@@ -1490,7 +1490,7 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* val
   if (dvals_done) *dvals_done = false;
   if (plan->U == 0 || N == 0 || (!dBp && !dB)) return SHIRO_OK;
   const bool cap = stream_capturing(s);
-  shiro_tuning_t t = tuned;
+  shiro_tuning_t t = dvals && Bp ? with_dots(tuned, N, dt) : tuned;
   SpmmArgs a{};
   a.ldx = lddy;
   a.ldd = dvals && Bp ? ldp : 0;

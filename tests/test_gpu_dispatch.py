@@ -90,3 +90,79 @@ def test_sampled_product_kernels(shiro, N, dtype):
             dvals = torch.full((A.nnz,), float("nan"), device="cuda")
             shiro.spmm_backward(plan, None, Gd, Bp, dvals=dvals)
             assert oracle.rel_err(dvals.cpu().numpy(), ref, den) <= 1e-5, (pad, t)
+
+
+def _reused(n=1 << 17, deg=20):
+    """2.6M nonzeros, 20 a row and 20 a column: rows gathered many times."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    step = n // deg
+    col = torch.randint(step, (n, deg), generator=g, device="cuda") + torch.arange(deg, device="cuda") * step
+    row_ptr = torch.arange(0, n * deg + 1, deg, device="cuda")
+    vals = torch.rand(n * deg, generator=g, device="cuda") + 0.1
+    return row_ptr, col, vals
+
+
+def _check_step(shiro, plan, col, vals, N, dtype, seed=0, pad=0):
+    """Forward, dBpacked and dvals of a pattern with the same number of
+    nonzeros in every row against float64 sums."""
+    n, deg = col.shape
+    U = plan.info()["U"]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+
+    def dense(rows):
+        out = torch.empty(rows * (N + pad) + pad, dtype=dtype, device="cuda")[pad:].view(rows, N + pad)[:, :N]
+        return out.copy_(torch.rand(rows, N, generator=g, device="cuda") + 0.1)
+
+    uc, _, cm = shiro.selection(plan)
+    cm = cm.long()
+    Bp, G = dense(U), dense(n)
+    Y, dBp = dense(n).fill_(float("nan")), dense(U).fill_(float("nan"))
+    dvals = torch.full_like(vals, float("nan"))
+    shiro.spmm(plan, vals, Bp, out=Y)
+    shiro.spmm_backward(plan, vals, G, Bp, dBpacked=dBp, dvals=dvals)
+    alone = torch.full_like(vals, float("nan"))
+    shiro.spmm_backward(plan, None, G, Bp, dvals=alone)
+    # every term is positive, so a result's size is its sum of absolute terms
+    rows = torch.arange(n, device="cuda").repeat_interleave(deg)
+    want = torch.zeros(n, N, dtype=torch.float64, device="cuda")
+    dwant = torch.zeros(U, N, dtype=torch.float64, device="cuda")
+    part = max(1, (1 << 26) // N)
+    for k0 in range(0, vals.numel(), part):
+        k = slice(k0, k0 + part)
+        v, b, y = vals[k, None].double(), Bp[cm[k]].double(), G[rows[k]].double()
+        want.index_add_(0, rows[k], v * b)
+        dwant.index_add_(0, cm[k], v * y)
+        dv = (b * y).sum(1)
+        for got in (dvals[k], alone[k]):
+            assert float(((got.double() - dv) / dv).abs().max()) <= TOL[torch.float32]
+    assert float(((Y.double() - want) / want).abs().max()) <= TOL[dtype]
+    assert float(((dBp.double() - dwant) / dwant).abs().max()) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,N,lanes", [(torch.float32, 72, 32), (torch.float32, 128, 16), (torch.float32, 320, 16),
+                                           (torch.bfloat16, 136, 32), (torch.bfloat16, 256, 16)])
+def test_tiles_of_reused_rows(shiro, dtype, N, lanes):
+    """256-byte tiles where rows are reused, but not for rows that one 512-byte
+    tile holds, and never where they would take the value gradients out of the
+    backward's walk (N = 320: five such tiles)."""
+    row_ptr, col, vals = _reused()
+    n = col.shape[0]
+    plan = shiro.partition(row_ptr, col.reshape(-1).int(), n, n, 1, 0)
+    shiro.select_rows(plan)
+    for k in ("spmm", "spmm_t"):
+        assert shiro.get_tuning(plan, k, N, dtype)["lanes"] == lanes
+    shiro.prepare(plan, N, dtype)
+    _check_step(shiro, plan, col, vals, N, dtype)
+    if N == 320:  # in the walk: the dots' error is that of sums over its tiles, and one launch less
+        from torch.profiler import ProfilerActivity, profile
+
+        Bp, G = torch.rand(plan.info()["U"], N, device="cuda"), torch.rand(n, N, device="cuda")
+        dBp, dvals = torch.empty_like(Bp), torch.empty_like(vals)
+        shiro.spmm_backward(plan, vals, G, Bp, dBpacked=dBp, dvals=dvals)
+        torch.cuda.synchronize()
+        with profile(activities=[ProfilerActivity.CUDA]) as prof:
+            shiro.spmm_backward(plan, vals, G, Bp, dBpacked=dBp, dvals=dvals)
+            torch.cuda.synchronize()
+        assert not any("k_sddmm" in e.key for e in prof.key_averages())
