@@ -293,6 +293,18 @@ static void pattern_sizes(shiro_plan plan, int kernel, int64_t* rows, int64_t* n
 // bfloat16 N = 260 677 / 438).  The row kernel has its own chunk, lanes, depth
 // and grid: with those of the walk 2^18 R-MAT took 585 to 2056 us instead of
 // 510 to 1471 at N = 288 to 511.
+//
+// Narrow rows of more than 2^20 nonzeros: the windowed walk (group_rows 3),
+// whose groups of 8 lanes (16 from 9 columns on) take a nonzero each, where the
+// walk's 64 lanes are nearly all idle and its gathers not whole dwords
+// (bfloat16, odd widths), or where a backward's short rows (fewer than two
+// nonzeros) make each of its row ends a wavefront's work.  Walk / windowed, us:
+// 2^18 R-MAT bfloat16 N = 3 forward 113 / 61, backward with value gradients 235
+// / 148, N = 12 backward 217 / 183; ER panel of 2^23 columns float32 N = 1
+// backward 340 / 214, N = 6 372 / 296.  Chunks of 64 items (a lane group's own;
+// 96 for 16 lanes), 256 for short rows: at N = 6 64, 128 and 256 took 152, 160
+// and 211 us on 2^18 R-MAT, 292, 312 and 296 on the ER panel.  At 2^20 nonzeros
+// and fewer the walk moves the values itself, which saves more.
 shiro_tuning_t default_tuning(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt) {
   shiro_tuning_t t;
   t.lanes = 32;
@@ -324,6 +336,17 @@ shiro_tuning_t default_tuning(shiro_plan plan, int kernel, int32_t N, shiro_dtyp
       t.unroll = 2;
       t.wg_per_cu = 8;
     }
+    return t;
+  }
+  // narrow rows
+  const bool few = nnz < 2 * std::max(rows, gathered);
+  const bool odd16 = dt == SHIRO_BF16 && N < 16 && (kernel == SHIRO_KERNEL_SPMM_T ? N != 8 : N % 2 == 1);
+  const bool odd32 = dt == SHIRO_F32 && kernel == SHIRO_KERNEL_SPMM_T && (N < 4 || (few && N < 12 && N % 4));
+  if (nnz > (1 << 20) && N > 0 && (odd16 || odd32)) {
+    t.group_rows = 3;
+    t.lanes = 64;
+    const int64_t slots = ceil_div(ceil_div((rows + nnz) * N, 1 << 22), 16) * 16;  // 32 MiB of them
+    t.chunk = (int32_t)std::min<int64_t>(256, std::max<int64_t>(slots, few ? (N < 8 ? 256 : 128) : (N < 8 ? 64 : 96)));
   }
   return t;
 }

@@ -166,3 +166,44 @@ def test_tiles_of_reused_rows(shiro, dtype, N, lanes):
             shiro.spmm_backward(plan, vals, G, Bp, dBpacked=dBp, dvals=dvals)
             torch.cuda.synchronize()
         assert not any("k_sddmm" in e.key for e in prof.key_averages())
+
+
+def _few(n_rows=1 << 16, deg=20, n_cols=1 << 21):
+    """1.3M nonzeros over 2M columns: a column holds 1.3 of them at most."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    step = n_cols // deg
+    col = torch.randint(step, (n_rows, deg), generator=g, device="cuda") + torch.arange(deg, device="cuda") * step
+    row_ptr = torch.arange(0, n_rows * deg + 1, deg, device="cuda")
+    vals = torch.rand(n_rows * deg, generator=g, device="cuda") + 0.1
+    return row_ptr, col, vals, n_cols
+
+
+@pytest.mark.parametrize("dtype,N,forward,backward", [
+    (torch.bfloat16, 1, 64, 64), (torch.bfloat16, 2, 0, 64), (torch.bfloat16, 7, 64, 64), (torch.bfloat16, 8, 0, 0),
+    (torch.bfloat16, 9, 96, 96), (torch.bfloat16, 12, 0, 96), (torch.bfloat16, 15, 96, 96), (torch.bfloat16, 17, 0, 0),
+    (torch.float32, 1, 0, 64), (torch.float32, 3, 0, 64), (torch.float32, 4, 0, 0), (torch.float32, 7, 0, 0)])
+def test_narrow_rows(shiro, dtype, N, forward, backward):
+    """Narrow products of patterns above 2^20 nonzeros: the windowed walk with
+    chunks of its own (0: the nonzero walk), on rows that are reused and on
+    rows that are not, whole rows and padded ones."""
+    row_ptr, col, vals = _reused()
+    n = col.shape[0]
+    plan = shiro.partition(row_ptr, col.reshape(-1).int(), n, n, 1, 0)
+    shiro.select_rows(plan)
+    for k, chunk in (("spmm", forward), ("spmm_t", backward)):
+        t = shiro.get_tuning(plan, k, N, dtype)
+        assert t["group_rows"] == (3 if chunk else 2) and (not chunk or t["chunk"] == chunk)
+    shiro.prepare(plan, N, dtype)
+    for pad in (0, 1):
+        _check_step(shiro, plan, col, vals, N, dtype, pad=pad)
+    out = torch.empty(n, N, dtype=dtype, device="cuda")
+    Bp = torch.rand(plan.info()["U"], N, device="cuda").to(dtype)
+    assert torch.equal(shiro.spmm_noalloc(plan, vals, Bp, out), shiro.spmm(plan, vals, Bp))
+    row_ptr, col, vals, n_cols = _few()
+    plan = shiro.partition(row_ptr, col.reshape(-1).int(), col.shape[0], n_cols, 1, 0)
+    shiro.select_rows(plan)
+    t = shiro.get_tuning(plan, "spmm_t", N, dtype)
+    short = bool(backward) or (dtype == torch.float32 and N < 12 and N % 4 != 0)
+    assert t["group_rows"] == (3 if short else 2) and (not short or t["chunk"] == (256 if N < 8 else 128))
+    _check_step(shiro, plan, col, vals, N, dtype)
