@@ -294,6 +294,17 @@ static void pattern_sizes(shiro_plan plan, int kernel, int64_t* rows, int64_t* n
 // and grid: with those of the walk 2^18 R-MAT took 585 to 2056 us instead of
 // 510 to 1471 at N = 288 to 511.
 //
+// Rows of one to two 512-byte tiles whose second tile is mostly idle, or which
+// are no whole 128-byte lines (the line at the tile's end is read in both
+// passes): the windowed walk, which reads them in one, 16 bytes a lane.  Walk /
+// windowed, us: 2^18 ER matrix float32 N = 136 forward 389 / 334, backward with
+// value gradients 543 / 426; ER panel of 2^23 columns N = 136 693 / 576 and 1404
+// / 1077, N = 200 869 / 790 and 1655 / 1434, but N = 192 (whole lines) 703 / 695
+// and 1390 / 1301, and on the 2^18 matrix 192 373 / 398.  Not on reused rows, where 256-byte tiles gain as much.  Two nonzeros in
+// flight in the bfloat16 backward, 4 and 2: N = 264 2^18 ER 474 / 465, panel
+// 1380 / 1256 (walk 612 and 1481).  From 2^18 partial rows on also their sum,
+// which reads each once (0.4M of them, N = 136: 133 / 85).
+//
 // Narrow rows of more than 2^20 nonzeros: the windowed walk (group_rows 3),
 // whose groups of 8 lanes (16 from 9 columns on) take a nonzero each, where the
 // walk's 64 lanes are nearly all idle and its gathers not whole dwords
@@ -322,8 +333,8 @@ shiro_tuning_t default_tuning(shiro_plan plan, int kernel, int32_t N, shiro_dtyp
   const int64_t unit = dt == SHIRO_F32 ? 1 : 2;       // elements in 4 bytes
   const int64_t half = 64 * unit, tile = 128 * unit;  // columns of 256 and 512 bytes
   if (reused && N >= tile) t.lanes = 16;
+  const bool pieces = N % (4 * unit) == 0, lines = N % (32 * unit) == 0;  // of 16 and 128 bytes
   if (kernel == SHIRO_KERNEL_SDDMM) {
-    const bool pieces = N % (4 * unit) == 0, lines = N % (32 * unit) == 0;
     auto fill = [&](int64_t w) { return 100 * N / (ceil_div((int64_t)N, w) * w); };  // per cent
     const bool wide = N <= 4 * tile && (N <= tile || !pieces || ((lines || reused) && fill(tile) >= 78));
     const bool narrow = reused && pieces && N >= tile && N <= 4 * half &&
@@ -338,7 +349,13 @@ shiro_tuning_t default_tuning(shiro_plan plan, int kernel, int32_t N, shiro_dtyp
     }
     return t;
   }
-  // narrow rows
+  const bool idle = N > tile && N < 2 * tile && (4 * (N - tile) <= tile || !lines);
+  if (nnz > (kernel == SHIRO_KERNEL_AGGREGATE_C ? 1 << 18 : 1 << 20) && !reused && pieces && idle) {
+    t.group_rows = 3;
+    t.lanes = 64;
+    if (kernel == SHIRO_KERNEL_SPMM_T && dt == SHIRO_BF16) t.unroll = 2;
+    return t;
+  }
   const bool few = nnz < 2 * std::max(rows, gathered);
   const bool odd16 = dt == SHIRO_BF16 && N < 16 && (kernel == SHIRO_KERNEL_SPMM_T ? N != 8 : N % 2 == 1);
   const bool odd32 = dt == SHIRO_F32 && kernel == SHIRO_KERNEL_SPMM_T && (N < 4 || (few && N < 12 && N % 4));

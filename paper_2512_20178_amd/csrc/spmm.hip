@@ -953,6 +953,24 @@ bool walk_fits(const SpmmArgs& a, shiro_dtype in_dt, shiro_dtype out_dt, const s
   return strides_32(a, in_dt, out_dt) && ceil_div(a.N, (int64_t)kWave * walk_vec(a.N, in_dt, t.lanes)) <= 65535;
 }
 
+// The windowed walk loads element by element (vec 1) where an operand's base or
+// stride is no multiple of 16 bytes; rows of more than 512 bytes then take the
+// walk, which reads any alignment whole (2^18 ER matrix, N = 136, bases off by 4
+// bytes: forward 537 us element by element, 407 in the walk; backward with value
+// gradients 1369 and 562).
+bool windowed_unaligned(const SpmmArgs& a, shiro_dtype in_dt, shiro_dtype out_dt, const shiro_tuning_t& t, int vec) {
+  const int unit = in_dt == SHIRO_F32 ? 1 : 2;
+  shiro_tuning_t w = t;
+  w.lanes = 32;
+  return t.group_rows == 3 && t.lds_rows == 0 && a.rid && vec == 1 && a.N > 128 * unit && a.N % (4 * unit) == 0 &&
+         walk_fits(a, in_dt, out_dt, w);
+}
+shiro_tuning_t as_walk(shiro_tuning_t t) {
+  t.group_rows = 2;
+  t.lanes = 32;
+  return t;
+}
+
 template <typename TIN, typename TOUT>
 int run_spmm_family(shiro_plan plan, shiro_tuning_t t, const WorkList* wl, SpmmArgs a, int vec,
                     hipStream_t s) {
@@ -1272,17 +1290,18 @@ int launch_pattern(shiro_plan plan, const shiro_tuning_t& t, const WorkList* wl,
   a.W = wl->W;
   a.R = (int32_t)R;
   a.N = N;
+  auto fit = [&](int v) { return windowed_unaligned(a, in_dt, out_dt, t, v) ? as_walk(t) : t; };
   if (in_dt == SHIRO_F32 && out_dt == SHIRO_F32) {
     const int v = vec_for<float>(N, {{X, ldx}, {Y, ldy}});
-    return run_spmm_family<float, float>(plan, t, wl, a, v, s);
+    return run_spmm_family<float, float>(plan, fit(v), wl, a, v, s);
   }
   if (in_dt == SHIRO_BF16 && out_dt == SHIRO_F32) {
     const int v = vec_for<bf16_t>(N, {{X, ldx}}) == 8 && aligned16<float>(Y, ldy) ? 8 : 1;
-    return run_spmm_family<bf16_t, float>(plan, t, wl, a, v, s);
+    return run_spmm_family<bf16_t, float>(plan, fit(v), wl, a, v, s);
   }
   if (in_dt == SHIRO_BF16 && out_dt == SHIRO_BF16) {
     const int v = vec_for<bf16_t>(N, {{X, ldx}, {Y, ldy}});
-    return run_spmm_family<bf16_t, bf16_t>(plan, t, wl, a, v, s);
+    return run_spmm_family<bf16_t, bf16_t>(plan, fit(v), wl, a, v, s);
   }
   return set_error(SHIRO_ERR_UNSUPPORTED, "dtype pair not supported (F32->F32, BF16->F32, BF16->BF16)");
 }
@@ -1513,6 +1532,12 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* val
   int v;
   if (dt == SHIRO_F32) v = vec_for<float>(N, {{dY, lddy}, {dBp, lddbp}, {dB, lddb}, {Bp, ldp}});
   else v = vec_for<bf16_t>(N, {{dY, lddy}, {dBp, lddbp}, {dB, lddb}, {Bp, ldp}});
+  a.rid = plan->tr.rid;
+  if (windowed_unaligned(a, dt, dt, t, v)) {
+    // (its tiles' dots need a set each: not in a capture that was prepared for one)
+    const int sets = dvals && Bp ? walk_dot_tiles(N, dt, as_walk(t)) : 1;
+    if (!cap || plan->tdvals_tiles >= sets || plan->tdvals_refused <= sets) t = as_walk(t);
+  }
   // dvals ride along when one column tile covers N, or (the walk) up to four
   // tiles, whose partial dots the scatter pass adds
   const int tiles = is_walk(t) ? walk_dot_tiles(N, dt, t) : 1;
@@ -1549,7 +1574,6 @@ int launch_spmm_t(shiro_plan plan, const shiro_tuning_t& tuned, const float* val
   a.idx = hot ? hot->walk_idx : plan->tr.row;
   a.hot_src = hot ? hot->hot_src : nullptr;
   a.n_hot = hot ? hot->H : 0;
-  a.rid = plan->tr.rid;
   a.out = dBp;
   a.scat = dB;
   a.scat_mode = db_overwrite ? 2 : 1;

@@ -207,3 +207,42 @@ def test_narrow_rows(shiro, dtype, N, forward, backward):
     short = bool(backward) or (dtype == torch.float32 and N < 12 and N % 4 != 0)
     assert t["group_rows"] == (3 if short else 2) and (not short or t["chunk"] == (256 if N < 8 else 128))
     _check_step(shiro, plan, col, vals, N, dtype)
+
+
+@pytest.mark.parametrize("dtype,N,windowed", [
+    (torch.float32, 128, False), (torch.float32, 132, True), (torch.float32, 160, True), (torch.float32, 192, False),
+    (torch.float32, 200, True), (torch.float32, 201, False), (torch.float32, 252, True), (torch.float32, 256, False),
+    (torch.bfloat16, 264, True), (torch.bfloat16, 260, False), (torch.bfloat16, 384, False)])
+def test_partly_filled_tiles(shiro, dtype, N, windowed):
+    """Rows of one to two tiles above 2^20 nonzeros: the windowed walk where
+    the second tile is mostly idle or rows are no whole lines; operands at odd
+    addresses run as well, eagerly and in a capture that was prepared for
+    aligned ones."""
+    row_ptr, col, vals, n_cols = _few(n_cols=1 << 19)
+    plan = shiro.partition(row_ptr, col.reshape(-1).int(), col.shape[0], n_cols, 1, 0)
+    shiro.select_rows(plan)
+    for k in ("spmm", "spmm_t"):
+        assert (shiro.get_tuning(plan, k, N, dtype)["group_rows"] == 3) == windowed
+    shiro.prepare(plan, N, dtype)
+    for pad in (0, 1):
+        _check_step(shiro, plan, col, vals, N, dtype, pad=pad)
+    fresh = shiro.partition(row_ptr, col.reshape(-1).int(), col.shape[0], n_cols, 1, 0)
+    U, _ = shiro.select_rows(fresh)
+    shiro.prepare(fresh, N, dtype)
+    n = col.shape[0]
+    store = [torch.rand(r * N + 1, device="cuda").to(dtype)[1:].view(r, N) for r in (U, n)]
+    Bp, G = store
+    Y, dBp, dvals = torch.empty_like(G), torch.empty_like(Bp), torch.zeros_like(vals)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        shiro.spmm(fresh, vals, Bp, out=Y)
+        shiro.spmm_backward(fresh, vals, G, Bp, dBpacked=dBp, dvals=dvals)
+    for _ in range(2):
+        graph.replay()
+        torch.cuda.synchronize()
+        tol = TOL[dtype]
+        assert float((Y.double() / shiro.spmm(plan, vals, Bp).double() - 1).abs().max()) <= 2 * tol
+        want, dv = torch.empty_like(Bp), torch.zeros_like(vals)
+        shiro.spmm_backward(plan, vals, G, Bp, dBpacked=want, dvals=dv)
+        assert float((dBp.double() - want.double()).abs().max() / want.double().abs().max()) <= 2 * tol
+        assert float(((dvals - dv) / dv).abs().max()) <= 1e-5
