@@ -503,6 +503,10 @@ struct TuneBuffers {
   }
 };
 
+// Raised when a tuning's fields come to mean another kernel: results timed for
+// the kernels before (2: group_rows 1 and 2 became the nonzero walk) then miss.
+constexpr int kTuneGeneration = 2;
+
 static std::string tune_key(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt) {
   hipDeviceProp_t prop;
   std::string name = "gpu";
@@ -511,7 +515,8 @@ static std::string tune_key(shiro_plan plan, int kernel, int32_t N, shiro_dtype 
     if (ch == ' ' || ch == ':') ch = '_';
   std::ostringstream os;
   os << name << "|rows=" << plan->rows << "|nnz=" << plan->nnz << "|U=" << plan->U
-     << "|P=" << plan->P << "|N=" << N << "|dt=" << (int)dt << "|k=" << kernel;
+     << "|P=" << plan->P << "|N=" << N << "|dt=" << (int)dt << "|g=" << kTuneGeneration
+     << "|k=" << kernel;
   return os.str();
 }
 
@@ -596,6 +601,8 @@ static int fit_chunk(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt, con
 
 static int tune_one(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt, TuneBuffers& b,
                     hipStream_t s) {
+  // one launch whatever the tuning (dots.hip)
+  if (kernel == SHIRO_KERNEL_SDDMM && dots_narrow(N)) return SHIRO_OK;
   const std::string key = tune_key(plan, kernel, N, dt);
   shiro_tuning_t cached;
   if (cache_lookup(key, &cached) && validate_tuning(kernel, N, dt, cached) == SHIRO_OK) {
@@ -627,10 +634,14 @@ static int tune_one(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt, Tune
     }
     return SHIRO_OK;
   };
-  // stage 1: work size and depth
+  // the default itself, then stage 1: work size and depth (which the nonzero
+  // walk has none of: the same launch again)
+  const shiro_tuning_t start = best;
+  SHIRO_TRY(consider(start));
   for (int chunk : {128, 256, 512, 1024, 2048})
     for (int unroll : {1, 2, 4}) {
-      shiro_tuning_t t = default_tuning(plan, kernel, N, dt);
+      shiro_tuning_t t = start;
+      if (is_walk(t) && unroll != t.unroll) continue;
       t.chunk = chunk;
       t.unroll = unroll;
       SHIRO_TRY(consider(t));
@@ -647,7 +658,7 @@ static int tune_one(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt, Tune
       for (int wg : {2, 4, 8, 16})
         for (int xcd : {0, 1}) {
           // the same launch as another candidate
-          const bool is_w = !walk || grp == 1 || grp == 2;
+          const bool is_w = grp == 1 || grp == 2;
           if (is_w && (wg != 16 || lanes == 64 || grp != (walk ? 2 : 1))) continue;
           shiro_tuning_t t = base;
           t.group_rows = grp;
@@ -690,6 +701,7 @@ static int tune_one(shiro_plan plan, int kernel, int32_t N, shiro_dtype dt, Tune
     for (int chunk : chunks)
       for (int unroll : {1, 2, 4}) {
         shiro_tuning_t t = base3;
+        if (is_walk(t) && unroll != t.unroll) continue;
         t.chunk = chunk;
         t.unroll = unroll;
         SHIRO_TRY(refine(t));

@@ -246,3 +246,26 @@ def test_partly_filled_tiles(shiro, dtype, N, windowed):
         shiro.spmm_backward(plan, vals, G, Bp, dBpacked=want, dvals=dv)
         assert float((dBp.double() - want.double()).abs().max() / want.double().abs().max()) <= 2 * tol
         assert float(((dvals - dv) / dv).abs().max()) <= 1e-5
+
+
+def test_tunings_of_earlier_kernels_are_not_applied(shiro, tmp_path, monkeypatch):
+    """A tuning file keeps results across libraries.  Lines written for kernels
+    that are gone (no generation in their key) are not applied; this library's
+    own are."""
+    A, N = synth.small_rmat(9, 8), 96
+    plan, U, Ad = _plan(shiro, A)
+    arch = torch.cuda.get_device_properties(0).gcnArchName.replace(" ", "_").replace(":", "_")
+    cache = tmp_path / "tune.txt"
+    old = [f"{arch}|rows={A.n_rows}|nnz={A.nnz}|U={U}|P=1|N={N}|dt=0|k={k} 4099 8 1 {g} 1 3" for k, g in ((0, 1), (1, 2), (2, 0))]
+    cache.write_text("\n".join(old) + "\n")
+    monkeypatch.setenv("SHIRO_TUNE_CACHE", str(cache))
+    shiro.autotune(plan, N)
+    got = {k: shiro.get_tuning(plan, k, N) for k in ("spmm", "spmm_t", "sddmm")}
+    assert all(t["chunk"] != 4099 for t in got.values())
+    lines = cache.read_text().splitlines()
+    assert lines[:3] == old and len(lines) == 6
+    keep = [ln.split(" ")[0] + " 4099 8 1 2 1 3 0" for ln in lines[3:5]]
+    cache.write_text("\n".join(keep) + "\n")
+    again, _, _ = _plan(shiro, A)
+    shiro.autotune(again, N, ops=("spmm",))
+    assert shiro.get_tuning(again, "spmm", N)["chunk"] == 4099
