@@ -259,20 +259,28 @@ static void pattern_sizes(shiro_plan plan, int kernel, int64_t* rows, int64_t* n
 // Defaults from sweeps on MI355X: the nonzero walk, except for the sampled
 // product where its last tile would be mostly idle.
 //
-// Chunk: at most 256 merge items (longer runs lengthen the serial sums and
-// the last round), fewer where that leaves the chip short of wavefronts: 256
+// Chunk: at most 256 merge items, fewer where that leaves the chip short of wavefronts: 256
 // CUs hold 8192 of them, and a chunk is a serial walk, so the aim is 16384
 // chunks, 16 items at least.  The 4096-vertex R-MAT (57K items, N = 32) took
 // 38 us backward at 256 and 28 at 16, 2^15 vertices (550K, N = 64) 58 at 256
-// and 43 at 32 to 64; from 2.2M items on 128 and 256 are alike.  Beyond that
-// no more chunks than leave the carry slots (2 N floats each) within the 32
-// MiB the allocation-free product has.
+// and 43 at 32 to 64; from 2.2M items on 128 and 256 are alike.  No more chunks
+// than leave the carry slots (2 N floats each) within the 32 MiB the
+// allocation-free product has, but never more than 256 items for that (the
+// 2^24 panel at N = 256 would need 272 and has 34 MB of slots).  256 is a middle:
+// the autotuner takes 2093 for the panel's float32 forward at N = 128 (297 us
+// against 312), 512 to 2048 for forwards of the 2^21 and 2^22 matrices, and 128
+// to 219 for most backwards.
 //
 // Tile: 256 bytes of a row at a time (two passes over the index streams at
 // 512-byte rows) where rows are gathered many times from more than the caches
 // hold, because twice as many of them then stay in a 4 MB L2: 2^21 GCN matrix
 // at N = 128 forward 6.45 -> 5.93 ms, backward 12.7 -> 11.8; 2^18 R-MAT (15
-// nonzeros a row) 188 -> 169 and 356 -> 328 us.  Otherwise 512: with few uses
+// nonzeros a row) 188 -> 169 and 356 -> 328 us.  What stays is the rows used
+// most, so columns have to be used unevenly: of uniform ones, 12 nonzeros each,
+// all occur, of an R-MAT's a third does not.  Uniform matrices lose (2^20 ER, 16
+// nonzeros a row, N = 128 1304 in one pass, 1394 in two, gradients 1746 and 1914;
+// 2^19 ER, 14 a row, N = 200 1023 in one of the windowed walk, 1322).  Otherwise
+// 512: with few uses
 // per row (2^24 panel, 3.4) or short rows (its backward, 3.4 nonzeros, 471
 // against 496 us) or cached matrices (2^16 R-MAT, 1M nonzeros, 47 against 51)
 // a second pass costs more than it saves; so it does for rows of less than 512
@@ -329,7 +337,8 @@ shiro_tuning_t default_tuning(shiro_plan plan, int kernel, int32_t N, shiro_dtyp
   const int64_t chunks = std::min<int64_t>(16384, (1 << 22) / std::max(N, 1));
   const int64_t c = ceil_div(rows + nnz, std::max<int64_t>(chunks, 1));
   t.chunk = (int32_t)std::min<int64_t>(256, std::max<int64_t>(16, ceil_div(c, 16) * 16));
-  const bool reused = nnz >= (1 << 21) && nnz >= 12 * rows && nnz >= 12 * gathered;
+  const bool uneven = 10 * std::max<int64_t>(plan->U, 0) < 9 * plan->n_cols;
+  const bool reused = uneven && nnz >= (1 << 21) && nnz >= 12 * rows && nnz >= 12 * gathered;
   const int64_t unit = dt == SHIRO_F32 ? 1 : 2;       // elements in 4 bytes
   const int64_t half = 64 * unit, tile = 128 * unit;  // columns of 256 and 512 bytes
   if (reused && N >= tile) t.lanes = 16;

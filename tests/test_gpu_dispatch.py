@@ -92,12 +92,13 @@ def test_sampled_product_kernels(shiro, N, dtype):
             assert oracle.rel_err(dvals.cpu().numpy(), ref, den) <= 1e-5, (pad, t)
 
 
-def _reused(n=1 << 17, deg=20):
-    """2.6M nonzeros, 20 a row and 20 a column: rows gathered many times."""
+def _reused(n=1 << 17, deg=20, part=2 / 3):
+    """2.6M nonzeros, 20 a row, on the given part of the columns: rows gathered
+    many times, unevenly where some columns are not used at all."""
     g = torch.Generator(device="cuda")
     g.manual_seed(3)
     step = n // deg
-    col = torch.randint(step, (n, deg), generator=g, device="cuda") + torch.arange(deg, device="cuda") * step
+    col = torch.randint(int(step * part), (n, deg), generator=g, device="cuda") + torch.arange(deg, device="cuda") * step
     row_ptr = torch.arange(0, n * deg + 1, deg, device="cuda")
     vals = torch.rand(n * deg, generator=g, device="cuda") + 0.1
     return row_ptr, col, vals
@@ -144,9 +145,14 @@ def _check_step(shiro, plan, col, vals, N, dtype, seed=0, pad=0):
 @pytest.mark.parametrize("dtype,N,lanes", [(torch.float32, 72, 32), (torch.float32, 128, 16), (torch.float32, 320, 16),
                                            (torch.bfloat16, 136, 32), (torch.bfloat16, 256, 16)])
 def test_tiles_of_reused_rows(shiro, dtype, N, lanes):
-    """256-byte tiles where rows are reused, but not for rows that one 512-byte
-    tile holds, and never where they would take the value gradients out of the
-    backward's walk (N = 320: five such tiles)."""
+    """256-byte tiles where rows are reused unevenly, but not for rows that one
+    512-byte tile holds, and never where they would take the value gradients out
+    of the backward's walk (N = 320: five such tiles)."""
+    row_ptr, col, vals = _reused(part=1)
+    n = col.shape[0]
+    plan = shiro.partition(row_ptr, col.reshape(-1).int(), n, n, 1, 0)
+    shiro.select_rows(plan)
+    assert shiro.get_tuning(plan, "spmm", N, dtype)["lanes"] == 32
     row_ptr, col, vals = _reused()
     n = col.shape[0]
     plan = shiro.partition(row_ptr, col.reshape(-1).int(), n, n, 1, 0)
@@ -269,3 +275,16 @@ def test_tunings_of_earlier_kernels_are_not_applied(shiro, tmp_path, monkeypatch
     again, _, _ = _plan(shiro, A)
     shiro.autotune(again, N, ops=("spmm",))
     assert shiro.get_tuning(again, "spmm", N)["chunk"] == 4099
+
+
+def _strided(rows, N, stride, seed, dtype=torch.float32):
+    """rows x N with `stride` elements between rows, filled from seed."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    t = torch.empty((rows - 1) * stride + N, dtype=dtype, device="cuda").as_strided((rows, N), (stride, 1))
+    t.copy_(torch.rand(rows, N, generator=g, device="cuda") + 0.1)
+    return t
+
+
+def _tight(t):
+    return t.contiguous() if t.stride(0) == t.shape[1] else t.clone(memory_format=torch.contiguous_format)
