@@ -288,3 +288,154 @@ def _strided(rows, N, stride, seed, dtype=torch.float32):
 
 def _tight(t):
     return t.contiguous() if t.stride(0) == t.shape[1] else t.clone(memory_format=torch.contiguous_format)
+
+
+@pytest.mark.parametrize("dtype,N,rows,stride", [
+    (torch.float32, 96, 3, (1 << 30) + 4),     # rows 4 GB apart: the row kernel
+    (torch.float32, 130, 3, (1 << 30) + 1),
+    (torch.bfloat16, 160, 3, (1 << 31) + 8),
+    (torch.float32, 96, 80, 1 << 24),          # 5 GB of rows: gathers of 64-bit offsets
+    (torch.float32, 33, 80, (1 << 24) + 1),
+    (torch.bfloat16, 160, 80, 1 << 25),
+    (torch.bfloat16, 31, 80, (1 << 25) + 1),
+])
+def test_rows_far_apart(shiro, dtype, N, rows, stride):
+    """Operands whose rows, or whole extent, lie beyond 32-bit byte offsets
+    give what tight copies of them give."""
+    A = _pattern(rows, rows, 5, density=0.5 if rows == 3 else 0.2)
+    plan, U, Ad = _plan(shiro, A)
+    tol = TOL[dtype]
+
+    def close(a, b, t):
+        a, b = a.double(), b.double()
+        return float(((a - b).abs() / b.abs().clamp_min(1e-30)).max()) <= t
+
+    Bp = _strided(U, N, stride, 1, dtype)
+    Y = shiro.spmm(plan, Ad.vals, Bp)
+    Bt = _tight(Bp)
+    assert close(Y, shiro.spmm(plan, Ad.vals, Bt), 2 * tol)
+    G = _strided(A.n_rows, N, stride, 2, dtype) if rows > 3 else (torch.rand(A.n_rows, N, device="cuda") + 0.1).to(dtype)
+    Gt = _tight(G)
+    want, dv = torch.empty_like(Bt), torch.zeros(A.nnz, device="cuda")
+    shiro.spmm_backward(plan, Ad.vals, Gt, Bt, dBpacked=want, dvals=dv)
+    got, gv = torch.empty_like(Bt), torch.zeros(A.nnz, device="cuda")
+    shiro.spmm_backward(plan, Ad.vals, G, Bp, dBpacked=got, dvals=gv)
+    assert close(got, want, 2 * tol) and close(gv, dv, 2e-5)
+    gv.fill_(float("nan"))
+    shiro.spmm_backward(plan, None, G, Bp, dvals=gv)
+    assert close(gv, dv, 2e-5)
+    del Bp, G
+    out = _strided(A.n_rows, N, stride, 3, dtype) if rows == 3 else torch.empty_like(Gt)
+    shiro.spmm(plan, Ad.vals, Bt, out=out)  # written rows far apart
+    assert close(_tight(out), shiro.spmm(plan, Ad.vals, Bt), 2 * tol)
+
+
+@pytest.mark.parametrize("N", [32, 64, 130, 200])
+def test_gradients_in_place_of_values(shiro, N):
+    """dvals may be the very array of the values (and so replace them): small
+    patterns whose walk would read and write through the permutation, and wider
+    ones."""
+    A = synth.small_rmat(10, 16)
+    plan, U, Ad = _plan(shiro, A)
+    Bp = synth.dense(U, N, 1, synth.STREAM_B).cuda()
+    G = synth.dense(A.n_rows, N, 2, synth.STREAM_DY).cuda()
+    want, dv = torch.empty(U, N, device="cuda"), torch.zeros(A.nnz, device="cuda")
+    shiro.spmm_backward(plan, Ad.vals, G, Bp, dBpacked=want, dvals=dv)
+    got, both = torch.empty(U, N, device="cuda"), Ad.vals.clone()
+    shiro.spmm_backward(plan, both, G, Bp, dBpacked=got, dvals=both)
+    assert torch.equal(got, want)
+    assert torch.equal(both, dv)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("N", [5, 33, 47, 65, 129, 255])
+def test_infinities_and_nan_stay_in_their_columns(shiro, N, dtype):
+    """Not-a-numbers and infinities in some columns, the shared columns of a
+    ragged tile's last lanes among them, reach exactly the results that their
+    columns and rows contribute to."""
+    A = _pattern(60, 70, N)
+    plan, U, Ad = _plan(shiro, A)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    Bp = (torch.rand(U, N, generator=g, device="cuda") + 0.1).to(dtype)
+    G = (torch.rand(60, N, generator=g, device="cuda") + 0.1).to(dtype)
+    uc, _, cm = shiro.selection(plan)
+    rows = torch.repeat_interleave(torch.arange(60, device="cuda"), Ad.row_ptr[1:] - Ad.row_ptr[:-1])
+    for col in sorted({0, N // 2, N - 4, N - 2, N - 1}):
+        X, Z = Bp.clone(), G.clone()
+        X[U // 2, col], Z[7, col] = float("nan"), float("inf")
+        Y = shiro.spmm(plan, Ad.vals, X)
+        hit = torch.zeros(60, dtype=torch.bool, device="cuda")
+        hit[rows[cm.long() == U // 2]] = True
+        bad = torch.isnan(Y)
+        assert torch.equal(bad[:, col], hit) and int(bad.sum()) == int(hit.sum())
+        dBp, dvals = torch.empty_like(X), torch.zeros(A.nnz, device="cuda")
+        shiro.spmm_backward(plan, Ad.vals, Z, X, dBpacked=dBp, dvals=dvals)
+        alone = torch.zeros(A.nnz, device="cuda")
+        shiro.spmm_backward(plan, None, Z, X, dvals=alone)
+        inf = torch.zeros(U, dtype=torch.bool, device="cuda")
+        inf[cm.long()[rows == 7]] = True
+        assert torch.equal(torch.isinf(dBp)[:, col], inf) and int((~torch.isfinite(dBp)).sum()) == int(inf.sum())
+        nan, infd = cm.long() == U // 2, rows == 7
+        for dv in (dvals, alone):
+            assert torch.equal(torch.isnan(dv), nan)
+            assert torch.equal(torch.isinf(dv), infd & ~nan)
+
+
+@pytest.mark.parametrize("dtype,N", [(torch.float32, 16), (torch.float32, 200), (torch.bfloat16, 40), (torch.bfloat16, 300)])
+def test_uninitialised_gradients_are_written_whole(shiro, dtype, N):
+    """Where every column of the matrix occurs, autograd hands the backward an
+    uninitialised dB, and where the plan holds every value an uninitialised
+    dvals: no stale entry is left, for rows in one chunk and rows cut by many,
+    one column tile and several."""
+    rng = np.random.default_rng(N)
+    n = 300
+    mask = rng.random((n, n)) < 0.03
+    mask[np.arange(n), np.arange(n)] = True  # every column occurs
+    mask[:, 17] = rng.random(n) < 0.9        # cut by many chunks
+    A = synth.from_dense_pattern((rng.uniform(0.1, 1, size=(n, n)) * mask).astype(np.float32), P=1, p=0, name="full")
+    plan, U, Ad = _plan(shiro, A)
+    assert U == n == plan.info()["n_cols"] and plan._whole
+    for chunk in (None, 16):
+        if chunk:
+            shiro.set_tuning(plan, "spmm_t", N, dtype, chunk=chunk)
+        B = synth.dense(n, N, 0, synth.STREAM_B).to(dtype).cuda()
+        G = synth.dense(n, N, 0, synth.STREAM_DY).to(dtype).cuda()
+        vals, Bl = Ad.vals.clone().requires_grad_(True), B.clone().requires_grad_(True)
+        Y = shiro.shiro_spmm(plan, vals, Bl)
+        stale = [torch.full((n * N,), float("nan"), dtype=dtype, device="cuda") for _ in range(4)]
+        stale += [torch.full((A.nnz,), float("nan"), device="cuda") for _ in range(4)]
+        del stale  # what the allocator hands out next
+        dvals, dB = torch.autograd.grad(Y, (vals, Bl), G)
+        Ac, Bn, Gn = oracle.Csr.from_synth(A), B.float().cpu().numpy(), G.float().cpu().numpy()
+        assert oracle.rel_err(dB.float().cpu().numpy(), oracle.spmm_t(Ac, Gn, None),
+                              oracle.spmm_t(Ac, Gn, None, abs_mode=True)) <= TOL[dtype]
+        assert oracle.rel_err(dvals.cpu().numpy(), oracle.sddmm(Ac, Gn, Bn, None),
+                              oracle.sddmm(Ac, Gn, Bn, None, abs_mode=True)) <= TOL[torch.float32]
+
+
+def test_full_size_kernels_agree(shiro):
+    """All 131072 rows, 1.2M packed columns and 4.15M values of the 2^24 R-MAT
+    panel: the nonzero walk against the row kernel and the windowed walk, which
+    sum in another order, componentwise against the sums of absolute terms."""
+    A = synth.config2(device=torch.device("cuda"))
+    N = 128
+    plan = shiro.partition(A.row_ptr, A.col, A.n_rows, A.n_cols, A.P, A.p)
+    U, _ = shiro.select_rows(plan)
+    B = synth.dense(A.n_cols, N, 0, synth.STREAM_B, device="cuda")
+    Bp = shiro.pack_B(plan, B)
+    del B
+    G = synth.dense(plan.info()["rows"], N, 0, synth.STREAM_DY, device="cuda")
+
+    def run(vals, Bp, G, grp):
+        for k in ("spmm", "spmm_t"):
+            shiro.set_tuning(plan, k, N, group_rows=grp, chunk=256, lanes=32, unroll=4)
+        Y, dBp, dv = shiro.spmm(plan, vals, Bp), torch.empty_like(Bp), torch.zeros_like(vals)
+        shiro.spmm_backward(plan, vals, G, Bp, dBpacked=dBp, dvals=dv)
+        return Y, dBp, dv
+
+    den = run(A.vals.abs(), Bp.abs(), G.abs(), 0)
+    walk = run(A.vals, Bp, G, 2)
+    for grp in (0, 3):
+        for a, b, d in zip(walk, run(A.vals, Bp, G, grp), den):
+            assert float(((a - b).abs() - 2 * TOL[torch.float32] * d).max()) <= 0
