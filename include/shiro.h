@@ -34,8 +34,10 @@
  *    captured into a HIP graph.
  *  - Matrices are row-major with a leading dimension (elements between rows):
  *    B is n_cols x N (ldb >= N), Bpacked is U x N, Y and dY are M x N, dB is
- *    n_cols x N.  Leading dimensions and base pointers that are multiples of
- *    16 bytes take the vector path; other values take a scalar path.
+ *    n_cols x N.  Any leading dimension and element-aligned base will do: the
+ *    nonzero walk reads rows of any alignment whole, the other kernels 16
+ *    bytes a lane where N, base and stride are multiples of 16 bytes and one
+ *    element a lane otherwise.
  *  - Sizes: n_rows, n_cols < 2^31; panel nonzeros < 2^31; all row * N address
  *    arithmetic is 64-bit.
  *  - The CSR is canonical: row_ptr non-decreasing from 0 to nnz, columns in
@@ -104,7 +106,7 @@ enum {
 #define SHIRO_CHECK_CSR 1u
 
 /* shiro_spmm modes */
-#define SHIRO_MODE_BATCHED 0u   /* all column blocks in one persistent launch, row-merged */
+#define SHIRO_MODE_BATCHED 0u   /* all column blocks in one launch, row-merged */
 #define SHIRO_MODE_PER_BLOCK 1u /* one launch per column block, summed in block order     */
 
 /* shiro_aggregate_c flags */
@@ -143,8 +145,8 @@ typedef struct {
                       * nonzeros; 1 or 2: the nonzero walk, a wavefront per
                       * chunk, every lane on every gathered row; 3: the windowed
                       * walk, each lane group of a wavefront on its own chunks.
-                      * Sampled product (SHIRO_KERNEL_SDDMM): 0 or 1, the walk
-                      * either way                                              */
+                      * Sampled product (SHIRO_KERNEL_SDDMM): 0 or 1; up to 64
+                      * columns a kernel of its own runs, whatever the tuning   */
   int32_t xcd_remap; /* 1: give each XCD a contiguous range of work            */
   int32_t wg_per_cu; /* persistent grid: workgroups per compute unit (not the
                       * nonzero walk, whose grid holds every chunk)             */
@@ -258,7 +260,7 @@ SHIRO_API int shiro_pack_B(shiro_plan plan, const void* d_B, int64_t ldb, int32_
  * index; the plan offsets by nz_begin).  Products and sums are float32; the
  * sum of each output element is taken in a fixed order.
  * Supported (in_dt -> out_dt): F32->F32, BF16->F32, BF16->BF16.
- * mode: SHIRO_MODE_BATCHED (one persistent launch over all blocks) or
+ * mode: SHIRO_MODE_BATCHED (one launch over all blocks) or
  * SHIRO_MODE_PER_BLOCK (one launch per block, accumulated in block order).
  * NOT_READY before select_rows; CAPTURING if capture is active and the
  * structures for (N, dtype, mode) were not prepared. */

@@ -7,8 +7,10 @@
 #include "plan.hpp"
 
 // Fixed work area: 32 MiB of carry slots (2 slots of N floats per merge-path
-// chunk).  That covers every per-rank panel of 2^17 rows and ~4M nonzeros
-// at N up to 256 with the tuned chunk sizes; larger patterns are rejected.
+// chunk).  That covers a panel of 2^17 rows and ~4M nonzeros at N up to 128
+// with the default chunks (at most 256 items: 17 MB at N = 128) and at N = 256
+// with chunks of 272 items or more (the default's 256 need 34 MB there);
+// larger patterns are rejected.
 // Host code never uses this name as an address: it stands for the host-side
 // shadow of the array; the device address comes from hipGetSymbolAddress.
 static constexpr int64_t kScratchFloats = int64_t(8) << 20;

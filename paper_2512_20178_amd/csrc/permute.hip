@@ -28,9 +28,20 @@ constexpr int kParts = (1 << kWinShift) / kPart;
 constexpr int kRun = 16384;              // CSR positions per workgroup
 constexpr int kFlight = 8;               // values in flight per thread
 
-// Patterns from here on use the staged order: below it the value array and
-// perm are mostly in the MALL and one pass is faster (4.2M nonzeros: 34 and 40
-// us direct).
+// Patterns from here on use the staged order.  Below about 4M nonzeros the value
+// array and perm are mostly in the MALL and one pass is faster; from 8M on two
+// are, and the order costs its set-up once.  Direct / staged, backward with value
+// gradients at N = 128 in us, and what the set-up adds to prepare in ms:
+//    3.9M (2^18 R-MAT)   330 / 351,      0.2
+//    8.4M (2^19 ER)     1053 / 951,      0.4   paid back after 5 backwards
+//   10.2M (2^20 R-MAT)  1111 / 1056,     0.4                   8
+//   12.6M (2^19 ER)     1523 / 1389,     0.6                   5
+//   16.8M (2^20 ER)     2108 / 1915,     0.8                   5
+//   20.0M (2^20 R-MAT)  1962 / 1917,     0.8                  19
+//   31.4M (2^20 R-MAT)  3221 / 2903,     1.4                   5
+//   97.6M (2^21 GCN)   11804 / 10577,    6.0                   5
+// The line lies above the crossing, so that patterns of a few million nonzeros,
+// which a program may make often (a rank's panel), do not pay the set-up.
 constexpr int64_t kStagedMin = (int64_t)12 << 20;
 
 __global__ __launch_bounds__(kBlock) void k_gather_vals(const int32_t* __restrict__ perm,

@@ -29,7 +29,7 @@ struct SpmmArgs {
   const int32_t* scat_idx;  // R
   const int32_t* chunk_row;  // W + 1
   const int32_t* chunk_nz;   // W + 1
-  const int32_t* rid;       // nnz: row of each nonzero (only for patterns without empty rows)
+  const int32_t* rid;       // nnz: row of each nonzero (both walks; without it the row kernel)
   const int32_t* hot_src;   // windowed walk: rows of X kept in LDS (idx = -(slot + 1) reads slot)
   int32_t n_hot;
   float* carry;             // [W][2][N]

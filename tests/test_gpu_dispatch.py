@@ -439,3 +439,23 @@ def test_full_size_kernels_agree(shiro):
     for grp in (0, 3):
         for a, b, d in zip(walk, run(A.vals, Bp, G, grp), den):
             assert float(((a - b).abs() - 2 * TOL[torch.float32] * d).max()) <= 0
+
+
+def test_default_chunks_of_a_wide_panel(shiro):
+    """Chunks end at 256 items also where the carry slots then need more than
+    the allocation-free product's 32 MiB (the 2^24 panel at N = 256: 34 MB): it
+    says so, and runs with chunks of 272."""
+    A = synth.config2(device=torch.device("cuda"))
+    N = 256
+    plan = shiro.partition(A.row_ptr, A.col, A.n_rows, A.n_cols, A.P, A.p)
+    U, _ = shiro.select_rows(plan)
+    rows = plan.info()["rows"]
+    assert shiro.get_tuning(plan, "spmm", N)["chunk"] == 256
+    shiro.prepare(plan, N, ops=("spmm",))
+    Bp, out = torch.rand(U, N, device="cuda"), torch.empty(rows, N, device="cuda")
+    with pytest.raises(shiro.ShiroError) as e:
+        shiro.spmm_noalloc(plan, A.vals, Bp, out)
+    assert e.value.name == "WORKSPACE"
+    shiro.set_tuning(plan, "spmm", N, chunk=272)
+    shiro.prepare(plan, N, ops=("spmm",))
+    assert torch.equal(shiro.spmm_noalloc(plan, A.vals, Bp, out), shiro.spmm(plan, A.vals, Bp))
