@@ -143,7 +143,7 @@ int ensure_rows_work(shiro_plan plan, int32_t chunk, bool allocate, hipStream_t 
       return set_error(SHIRO_ERR_CAPTURING,
                        "work list for chunk " + std::to_string(chunk) + " not prepared before capture");
     WorkList wl;
-    SHIRO_TRY(build_worklist(plan->row_ptr, plan->rows, plan->nnz, chunk, &wl, s));
+    SHIRO_TRY(build_worklist(plan, plan->row_ptr, plan->rows, plan->nnz, chunk, &wl, s));
     it = plan->rows_work.emplace(chunk, wl).first;
   }
   *out = &it->second;
@@ -159,8 +159,8 @@ int ensure_rb_work(shiro_plan plan, int which, int32_t chunk, bool allocate, hip
       return set_error(SHIRO_ERR_CAPTURING,
                        "row-based work list for chunk " + std::to_string(chunk) + " not prepared before capture");
     WorkList wl;
-    if (which == 0) SHIRO_TRY(build_worklist(plan->rb.ptr, plan->rb.R, plan->nnz, chunk, &wl, s));
-    else SHIRO_TRY(build_worklist(plan->rb.agg_ptr, plan->rows, plan->rb.R, chunk, &wl, s));
+    if (which == 0) SHIRO_TRY(build_worklist(plan, plan->rb.ptr, plan->rb.R, plan->nnz, chunk, &wl, s));
+    else SHIRO_TRY(build_worklist(plan, plan->rb.agg_ptr, plan->rows, plan->rb.R, chunk, &wl, s));
     it = m.emplace(chunk, wl).first;
   }
   *out = &it->second;
@@ -175,7 +175,7 @@ int ensure_cols_work(shiro_plan plan, int32_t chunk, bool allocate, hipStream_t 
       return set_error(SHIRO_ERR_CAPTURING,
                        "transposed work list for chunk " + std::to_string(chunk) + " not prepared before capture");
     WorkList wl;
-    SHIRO_TRY(build_worklist(plan->tr.ptr, plan->U, plan->nnz, chunk, &wl, s));
+    SHIRO_TRY(build_worklist(plan, plan->tr.ptr, plan->U, plan->nnz, chunk, &wl, s));
     it = plan->cols_work.emplace(chunk, wl).first;
   }
   *out = &it->second;
@@ -1114,10 +1114,12 @@ SHIRO_API int shiro_prepare(shiro_plan plan, int32_t N, shiro_dtype dt, uint32_t
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   if (stream_capturing(s)) return set_error(SHIRO_ERR_CAPTURING, "prepare: stream is capturing");
   const WorkList* wl;
+  int64_t slots = 0;  // the largest carry area of the calls prepared for, allocated once
+  auto carry_for = [&](int64_t W) { slots = std::max(slots, W * 2 * N); };
   if (ops & SHIRO_OP_SPMM) {
     const shiro_tuning_t t = tuning_for(plan, SHIRO_KERNEL_SPMM, N, dt);
     SHIRO_TRY(ensure_rows_work(plan, t.chunk, true, s, &wl));
-    SHIRO_TRY(ensure_carry(plan, (int64_t)wl->W * 2 * N, true));
+    carry_for(wl->W);
     SHIRO_TRY(ensure_row_rid(plan, true, s));
     const HotRows* hot;
     if (t.group_rows == 3 && t.lds_rows > 0) SHIRO_TRY(ensure_hot(plan, SHIRO_KERNEL_SPMM, t.lds_rows, true, s, &hot));
@@ -1128,7 +1130,7 @@ SHIRO_API int shiro_prepare(shiro_plan plan, int32_t N, shiro_dtype dt, uint32_t
     SHIRO_TRY(reserve_tdvals(plan, is_walk(t) ? std::max(walk_dot_tiles(N, dt, with_dots(t, N, dt)), 1) : 1, true));
     SHIRO_TRY(build_transposed(plan, s));
     SHIRO_TRY(ensure_cols_work(plan, t.chunk, true, s, &wl));
-    SHIRO_TRY(ensure_carry(plan, (int64_t)wl->W * 2 * N, true));
+    carry_for(wl->W);
     const HotRows* hot;
     if (t.group_rows == 3 && t.lds_rows > 0) SHIRO_TRY(ensure_hot(plan, SHIRO_KERNEL_SPMM_T, t.lds_rows, true, s, &hot));
     const shiro_tuning_t t2 = tuning_for(plan, SHIRO_KERNEL_SDDMM, N, dt);
@@ -1142,15 +1144,16 @@ SHIRO_API int shiro_prepare(shiro_plan plan, int32_t N, shiro_dtype dt, uint32_t
       const shiro_tuning_t t =
           tuning_for(plan, which == 0 ? SHIRO_KERNEL_PARTIAL_C : SHIRO_KERNEL_AGGREGATE_C, N, dt);
       SHIRO_TRY(ensure_rb_work(plan, which, t.chunk, true, s, &wl));
-      SHIRO_TRY(ensure_carry(plan, (int64_t)wl->W * 2 * N, true));
+      carry_for(wl->W);
     }
   }
   if (ops & SHIRO_OP_PER_BLOCK) {
     if (plan->vmap) return set_error(SHIRO_ERR_UNSUPPORTED, "prepare: per-block mode is not available on subset plans");
     SHIRO_TRY(build_per_block(plan, s));
-    SHIRO_TRY(ensure_carry(plan, (int64_t)plan->pb.max_W * 2 * N, true));
+    carry_for(plan->pb.max_W);
     if (dt == SHIRO_BF16) SHIRO_TRY(ensure_acc32(plan, plan->rows * (int64_t)N, true));
   }
+  SHIRO_TRY(ensure_carry(plan, slots, true));
   SHIRO_HIP(hipStreamSynchronize(s));
   return SHIRO_OK;
 }

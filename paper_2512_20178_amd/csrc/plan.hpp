@@ -249,7 +249,7 @@ int launch_dots(const int32_t* idx, const int32_t* rid, const void* D, int64_t l
                 const int32_t* map, float* out, int64_t nnz, int32_t N, shiro_dtype dt, hipStream_t s);
 
 // ---- spmm.hip ---------------------------------------------------------------
-int build_worklist(const int64_t* ptr, int64_t R, int64_t nnz, int32_t chunk, WorkList* wl,
+int build_worklist(shiro_plan plan, const int64_t* ptr, int64_t R, int64_t nnz, int32_t chunk, WorkList* wl,
                    hipStream_t s);
 int build_transposed(shiro_plan plan, hipStream_t s);
 int build_segments(shiro_plan plan, hipStream_t s);

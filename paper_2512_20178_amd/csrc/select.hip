@@ -110,20 +110,14 @@ constexpr int kBinShift = 17;                          // column ids per bin: 2^
 constexpr int kBinWords = 1 << (kBinShift - 5);        // 4096 bitmap words (16 KB)
 
 // Bin of each column id (the sort key of the bin-major copy).
-__global__ void k_bin_keys(const int32_t* __restrict__ col, int64_t nnz, uint32_t* __restrict__ key) {
-  for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < nnz;
-       k += (int64_t)gridDim.x * blockDim.x)
-    key[k] = (uint32_t)col[k] >> kBinShift;
-}
-
-// off[b] = first entry of bin b in the sorted keys (lower bound), off[nbins] = n.
-__global__ void k_bin_off(const uint32_t* __restrict__ skey, int64_t n, int64_t nbins, int64_t* __restrict__ off) {
+// off[b] = first entry of bin b in the bin-major ids (lower bound), off[nbins] = n.
+__global__ void k_bin_off(const int32_t* __restrict__ bcol, int64_t n, int64_t nbins, int64_t* __restrict__ off) {
   for (int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; b <= nbins;
        b += (int64_t)gridDim.x * blockDim.x) {
     int64_t lo = 0, hi = n;
     while (lo < hi) {
       const int64_t mid = (lo + hi) >> 1;
-      if ((int64_t)skey[mid] < b) lo = mid + 1; else hi = mid;
+      if ((int64_t)((uint32_t)bcol[mid] >> kBinShift) < b) lo = mid + 1; else hi = mid;
     }
     off[b] = lo;
   }
@@ -369,20 +363,15 @@ static int build_bins(shiro_plan plan, hipStream_t s) {
   }
   const int64_t nbins = ceil_div(plan->n_cols, (int64_t)1 << kBinShift);
   auto al = [](int64_t b) { return (b + 255) / 256 * 256; };
-  SHIRO_TRY(ensure_scratch(plan, 2 * al(nnz * 4) + al((nbins + 1) * 8) + sort_scratch_bytes(nnz)));
-  char* p = reinterpret_cast<char*>(plan->scratch);
-  uint32_t* key = reinterpret_cast<uint32_t*>(p);
-  uint32_t* skey = reinterpret_cast<uint32_t*>(p + al(nnz * 4));
-  int64_t* off = reinterpret_cast<int64_t*>(p + 2 * al(nnz * 4));
-  void* tmp = p + 2 * al(nnz * 4) + al((nbins + 1) * 8);
+  SHIRO_TRY(ensure_scratch(plan, al((nbins + 1) * 8) + sort_scratch_bytes(nnz)));
+  int64_t* off = reinterpret_cast<int64_t*>(plan->scratch);
+  void* tmp = reinterpret_cast<char*>(plan->scratch) + al((nbins + 1) * 8);
   SHIRO_TRY(dev_alloc_n(&plan->bcol, nnz));
-  k_bin_keys<<<grid_for(nnz), kBlock, 0, s>>>(plan->col, nnz, key);
-  SHIRO_LAUNCH_CHECK();
   int bits = 0;
   while (bits < 32 && ((int64_t)1 << bits) < nbins) ++bits;
-  SHIRO_TRY(radix_sort_pairs(key, reinterpret_cast<const uint32_t*>(plan->col), skey,
-                             reinterpret_cast<uint32_t*>(plan->bcol), nnz, bits, tmp, s));
-  k_bin_off<<<grid_for(nbins + 1), kBlock, 0, s>>>(skey, nnz, nbins, off);
+  SHIRO_TRY(radix_sort_keys(reinterpret_cast<const uint32_t*>(plan->col), reinterpret_cast<uint32_t*>(plan->bcol), nnz,
+                            kBinShift, bits, tmp, s));
+  k_bin_off<<<grid_for(nbins + 1), kBlock, 0, s>>>(plan->bcol, nnz, nbins, off);
   SHIRO_LAUNCH_CHECK();
   std::vector<int64_t> h((size_t)nbins + 1);
   SHIRO_HIP(hipMemcpyAsync(h.data(), off, (size_t)(nbins + 1) * 8, hipMemcpyDeviceToHost, s));

@@ -1034,7 +1034,7 @@ int run_spmm_family(shiro_plan plan, shiro_tuning_t t, const WorkList* wl, SpmmA
 // ===========================================================================
 // host entry points
 // ===========================================================================
-static int fill_worklist(const int64_t* ptr, int64_t R, int64_t nnz, int32_t chunk, WorkList* wl, char** tmp,
+static int fill_worklist(shiro_plan plan, const int64_t* ptr, int64_t R, int64_t nnz, int32_t chunk, WorkList* wl,
                          hipStream_t s) {
   wl->chunk = chunk;
   wl->W = (int32_t)ceil_div(R + nnz, chunk);
@@ -1046,15 +1046,16 @@ static int fill_worklist(const int64_t* ptr, int64_t R, int64_t nnz, int32_t chu
   wl->nsplit = 0;
   wl->nsmall = 0;
   if (wl->W == 0) return SHIRO_OK;
-  // list of rows cut by chunk boundaries (in one temporary block)
+  // list of rows cut by chunk boundaries
   const int64_t W = wl->W;
   const int64_t last_bytes = (W * 4 + 255) / 256 * 256, pos_bytes = ((W + 1) * 8 + 255) / 256 * 256;
-  SHIRO_TRY(dev_alloc(reinterpret_cast<void**>(tmp), last_bytes + pos_bytes + scan_scratch_bytes(W)));
-  int32_t* last = reinterpret_cast<int32_t*>(*tmp);
-  int64_t* pos = reinterpret_cast<int64_t*>(*tmp + last_bytes);
+  SHIRO_TRY(ensure_scratch(plan, last_bytes + pos_bytes + scan_scratch_bytes(W)));
+  char* tmp = reinterpret_cast<char*>(plan->scratch);
+  int32_t* last = reinterpret_cast<int32_t*>(tmp);
+  int64_t* pos = reinterpret_cast<int64_t*>(tmp + last_bytes);
   k_split_last<<<grid_for(W, 1 << 20), kBlock, 0, s>>>(ptr, (int32_t)R, wl->chunk_row, wl->chunk_nz, wl->W, last);
   SHIRO_LAUNCH_CHECK();
-  SHIRO_TRY(scan_generic(SplitCount{last}, W, SplitPlace{pos}, pos + W, *tmp + last_bytes + pos_bytes, s));
+  SHIRO_TRY(scan_generic(SplitCount{last}, W, SplitPlace{pos}, pos + W, tmp + last_bytes + pos_bytes, s));
   int64_t n = 0;
   SHIRO_HIP(hipMemcpyAsync(&n, pos + W, 8, hipMemcpyDeviceToHost, s));
   SHIRO_HIP(hipStreamSynchronize(s));
@@ -1069,11 +1070,9 @@ static int fill_worklist(const int64_t* ptr, int64_t R, int64_t nnz, int32_t chu
   return SHIRO_OK;
 }
 
-int build_worklist(const int64_t* ptr, int64_t R, int64_t nnz, int32_t chunk, WorkList* wl,
+int build_worklist(shiro_plan plan, const int64_t* ptr, int64_t R, int64_t nnz, int32_t chunk, WorkList* wl,
                    hipStream_t s) {
-  char* tmp = nullptr;
-  const int rc = fill_worklist(ptr, R, nnz, chunk, wl, &tmp, s);
-  dev_free(tmp);
+  const int rc = fill_worklist(plan, ptr, R, nnz, chunk, wl, s);
   if (rc != SHIRO_OK) {  // nothing is kept unless every step succeeds
     dev_free(wl->chunk_row);
     dev_free(wl->chunk_nz);
@@ -1099,12 +1098,11 @@ static int fill_transposed(shiro_plan plan, hipStream_t s) {
         [] __device__(int64_t, int64_t, int64_t) {}, tr.ptr, nullptr, s);
     return SHIRO_OK;
   }
-  // scratch: iota values + sort scratch; the sorted keys are the entries' rows
-  const int64_t need = (nnz * 4 + 256) + sort_scratch_bytes(nnz);
-  SHIRO_TRY(ensure_scratch(plan, need));
-  char* p = reinterpret_cast<char*>(plan->scratch);
-  uint32_t* iota = reinterpret_cast<uint32_t*>(p);
-  void* sort_tmp = p + (nnz * 4 + 256) / 256 * 256;
+  // the sorted keys are the entries' rows; the sorted values' input lives where
+  // the panel rows go afterwards
+  SHIRO_TRY(ensure_scratch(plan, sort_scratch_bytes(nnz)));
+  uint32_t* iota = reinterpret_cast<uint32_t*>(tr.row);
+  void* sort_tmp = plan->scratch;
   uint32_t* skeys = reinterpret_cast<uint32_t*>(tr.rid);
   k_iota<<<grid_for(nnz), kBlock, 0, s>>>(iota, nnz);
   SHIRO_LAUNCH_CHECK();
@@ -1704,7 +1702,7 @@ int build_per_block(shiro_plan plan, hipStream_t s) {
     const int64_t nq = h_ptr[off[q + 1]] - h_ptr[off[q]];
     if (nq == 0) continue;
     const int32_t chunk = (int32_t)std::min<int64_t>(std::max<int64_t>(ceil_div(Rq + nq, workers), 16), 4096);
-    SHIRO_TRY(build_worklist(pb.ptr + off[q] + q, Rq, nq, chunk, &pb.work[q], s));
+    SHIRO_TRY(build_worklist(plan, pb.ptr + off[q] + q, Rq, nq, chunk, &pb.work[q], s));
     pb.max_W = std::max(pb.max_W, pb.work[q].W);
   }
   pb.nz_off.assign((size_t)P + 1, 0);

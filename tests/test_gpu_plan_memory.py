@@ -283,3 +283,39 @@ def test_launch_errors_of_subset_plans_are_reported(shiro):
         torch.cuda.synchronize()
         plan.close()
     assert codes[0] == codes[1]
+
+
+@pytest.mark.parametrize("N", [32, 130, 256])
+def test_prepare_gives_nothing_back(shiro, N):
+    """Preparing a plan's product and backward allocates what stays and nothing
+    else: no temporary blocks, no buffer that a later step of it replaces."""
+    A = synth.small_rmat(13, 16)
+    Ad = A.to(torch.device("cuda"))
+    with arena(shiro) as a:
+        plan = shiro.partition(Ad.row_ptr, Ad.col, A.n_rows, A.n_cols, 1, 0)
+        shiro.select_rows(plan)
+        before = len(a.freed)
+        shiro.prepare(plan, N)
+        assert len(a.freed) == before
+        _backward(shiro, plan, Ad.vals, N)
+        assert len(a.freed) == before
+        plan.close()
+        assert not a.live
+
+
+def test_whole_plan_memory(shiro):
+    """A plan of 13M nonzeros, from partition to the prepared backward: 49 bytes
+    a nonzero (column ids three times, 9 of sort scratch, the transposed
+    pattern, row ids, values and gradients, the staged order) beside the row
+    and column arrays, work lists and carry slots."""
+    case = _large()
+    row_ptr, col, vals, _, _ = case
+    n, nnz = col.shape[0], vals.numel()
+    with arena(shiro) as a:
+        plan = shiro.partition(row_ptr, col.reshape(-1).int(), n, n, 1, 0)
+        shiro.select_rows(plan)
+        shiro.prepare(plan, 1)
+        assert sum(a.asked) <= 50 * nnz + 32 * n + (16 << 20)
+        _check_large(shiro, plan, case)
+        plan.close()
+        assert not a.live
