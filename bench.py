@@ -246,8 +246,10 @@ def main():
         lanes //= 2
     if tb["group_rows"] == 3 and tb["unroll"] == 1 and tdt == torch.float32 and lanes >= 16:
         kb = "k_spmm_win_w8"
+    # the value permutations: direct, or through the staged order of large patterns
+    perm = ("k_gather_vals", "k_scatter_vals") if nnz < 12 << 20 else ("k_stage_runs + k_stage_window",) * 2
     kernels_of = {"pack_B": "k_pack", "spmm": f"{kf} + k_fixup",
-                  "backward": f"k_gather_vals + {kb}<dot> + k_fixup + k_scatter_vals"}
+                  "backward": f"{perm[0]} + {kb}<dot> + k_fixup + {perm[1]}"}
     roofline = {"bound": "hbm", "kernel": f"{dom} ({kernels_of[dom]})", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "algorithmic_bytes": int(alg[dom]), "duration_us": round(kern_us[dom], 2)}

@@ -259,9 +259,9 @@ static void pattern_sizes(shiro_plan plan, int kernel, int64_t* rows, int64_t* n
 // Defaults from sweeps on MI355X: the nonzero walk, except for the sampled
 // product where its last tile would be mostly idle.
 //
-// Chunk: at most 256 merge items, fewer where that leaves the chip short of wavefronts: 256
-// CUs hold 8192 of them, and a chunk is a serial walk, so the aim is 16384
-// chunks, 16 items at least.  The 4096-vertex R-MAT (57K items, N = 32) took
+// Chunk: at most 256 merge items, fewer where that leaves the chip short of
+// wavefronts: 256 CUs hold 8192 of them, and a chunk is a serial walk, so the
+// aim is 16384 chunks, 16 items at least.  The 4096-vertex R-MAT (57K items, N = 32) took
 // 38 us backward at 256 and 28 at 16, 2^15 vertices (550K, N = 64) 58 at 256
 // and 43 at 32 to 64; from 2.2M items on 128 and 256 are alike.  No more chunks
 // than leave the carry slots (2 N floats each) within the 32 MiB the
@@ -274,17 +274,19 @@ static void pattern_sizes(shiro_plan plan, int kernel, int64_t* rows, int64_t* n
 // Tile: 256 bytes of a row at a time (two passes over the index streams at
 // 512-byte rows) where rows are gathered many times from more than the caches
 // hold, because twice as many of them then stay in a 4 MB L2: 2^21 GCN matrix
-// at N = 128 forward 6.45 -> 5.93 ms, backward 12.7 -> 11.8; 2^18 R-MAT (15
-// nonzeros a row) 188 -> 169 and 356 -> 328 us.  What stays is the rows used
-// most, so columns have to be used unevenly: of uniform ones, 12 nonzeros each,
-// all occur, of an R-MAT's a third does not.  Uniform matrices lose (2^20 ER, 16
-// nonzeros a row, N = 128 1304 in one pass, 1394 in two, gradients 1746 and 1914;
-// 2^19 ER, 14 a row, N = 200 1023 in one of the windowed walk, 1322).  Otherwise
-// 512: with few uses
-// per row (2^24 panel, 3.4) or short rows (its backward, 3.4 nonzeros, 471
-// against 496 us) or cached matrices (2^16 R-MAT, 1M nonzeros, 47 against 51)
-// a second pass costs more than it saves; so it does for rows of less than 512
-// bytes, which one pass reads whole (2^19 normalised R-MAT, 8M nonzeros, N = 72:
+// at N = 128 forward 6.45 -> 5.93 ms, backward 12.7 -> 11.8 (with the direct
+// value permutation); 2^18 R-MAT (15 nonzeros a row) 188 -> 169 and 356 -> 328
+// us; 2^19 R-MAT of 5 to 16 nonzeros a row (13 to 28 uses a gathered row) gains
+// 9 to 15%, the lowest of them outside the rule, which asks for 12 of both.
+// What stays is the rows used most, so columns have to be used unevenly: of
+// uniform ones, 12 nonzeros each, all occur, of an R-MAT's a third does not.
+// Uniform matrices lose (2^20 ER, 16 nonzeros a row, N = 128 1304 us in one pass,
+// 1394 in two, backward 1746 and 1914; 2^19 ER, 14 a row, N = 200 1032 in one
+// pass of the windowed walk, 1322 in four).  Otherwise 512: with few uses per
+// row (2^24 panel, 3.4) or short rows (its backward, 3.4 nonzeros, 471 against
+// 496 us) or cached matrices (2^16 R-MAT, 1M nonzeros, 47 against 51) a second
+// pass costs more than it saves; so it does for rows of less than 512 bytes,
+// which one pass reads whole (2^19 normalised R-MAT, 8M nonzeros, N = 72:
 // forward 283 us in one pass, 375 in two, gradients 535 and 624; N = 100 380
 // and 455; bfloat16 N = 136 287 and 393).
 //

@@ -10,21 +10,30 @@
 // changes.  Where rows end is one bit mask per window (a row id compared with
 // its neighbour lane's).
 //
-// What bounds it: on matrices larger than the caches the rows that miss L2
-// (about 7 TB/s cross the fabric); on L2-resident rows the L2 itself at N >=
-// 128 (15 TB/s of rows) and latency below.  Why this split: the walk it
+// What bounds it: on matrices larger than the caches the rows that miss L2.
+// Counted (fetched and written bytes over the kernel's time): forwards 7.1 TB/s
+// on the 2^24 R-MAT panel, 6.8 in bfloat16, 7.3 on the 2^21 GCN matrix, which is
+// the rate of random rows across the fabric; backwards with dots 5.8 and 5.7,
+// 7.0 on the ER panel at N = 128.  On L2-resident rows (8192 of them, 512 uses
+// each) the L2 itself at N >= 128 (16 TB/s of rows) and latency below (11 cycles
+// a nonzero and CU from 16 to 64 columns).  Why this split: the walk it
 // replaced gave every lane group a chunk of its own, with three vector loads
 // of indices per gather, divergent row ends, 118 registers, and one column
 // per lane at widths that are no multiple of 16 bytes.  Scalar loads of the
 // three streams instead of the windows were tried first: the scalar cache
 // fills one 64-byte line in about 36 cycles, 14 to 17 cycles per nonzero and
 // CU on L2-resident rows against 11.
-//   before -> after, us (MI355X; backwards with both value permutations)
-//   2^24 R-MAT panel, N = 128  f32 forward 331 -> 314, backward 647 -> 470
-//                              bf16 forward 223 -> 172, backward 450 -> 292
-//   ER panel, N = 64           f32 forward 311 -> 240, backward 612 -> 557
-//   2^18 R-MAT, N = 47         f32 forward 424 -> 98, backward 502 -> 211
-//   2^21 GCN matrix, N = 128   f32 forward 6.57 -> 6.44 ms, backward 14.0 -> 12.6
+//   before -> after, us (MI355X, each call repeated alone; backwards with both
+//   value permutations)
+//   2^24 R-MAT panel, N = 128  f32 forward 323 -> 306, backward 646 -> 467
+//                              bf16 forward 208 -> 172, backward 453 -> 298
+//   ER panel, N = 64           f32 forward 281 -> 238, backward 614 -> 557 (the
+//                              forward 276 when the pack has just run)
+//   2^18 R-MAT, N = 47         f32 forward 331 -> 97, backward 418 -> 208
+//   2^21 GCN matrix, N = 128   f32 forward 6.67 -> 5.67 ms, backward 14.6 -> 10.5
+//                              (256-byte tiles and the staged value order in it)
+// Widths that leave most of its lanes or of its last tile idle run elsewhere
+// (default_tuning).
 #pragma once
 
 #include <type_traits>
