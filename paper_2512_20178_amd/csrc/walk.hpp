@@ -11,10 +11,10 @@
 // its neighbour lane's).
 //
 // What bounds it: on matrices larger than the caches the rows that miss L2.
-// Counted (fetched and written bytes over the kernel's time): forwards 7.1 TB/s
-// on the 2^24 R-MAT panel, 6.8 in bfloat16, 7.3 on the 2^21 GCN matrix, which is
-// the rate of random rows across the fabric; backwards with dots 5.8 and 5.7,
-// 7.0 on the ER panel at N = 128.  On L2-resident rows (8192 of them, 512 uses
+// Counted (fetched and written bytes over the kernel's time): forwards 7.0 TB/s
+// on the 2^24 R-MAT panel, 6.8 in bfloat16, 7.2 on the 2^21 GCN matrix, which is
+// the rate of random rows across the fabric; backwards with dots 5.8 and 5.3
+// (they also wait for the rows they dot with), 7.0 on the ER panel at N = 128.  On L2-resident rows (8192 of them, 512 uses
 // each) the L2 itself at N >= 128 (16 TB/s of rows) and latency below (11 cycles
 // a nonzero and CU from 16 to 64 columns).  Why this split: the walk it
 // replaced gave every lane group a chunk of its own, with three vector loads
